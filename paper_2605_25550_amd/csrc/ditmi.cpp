@@ -643,7 +643,8 @@ struct AdaJob {
 dit_status run_adaln(const dit_shape* s, const float* cond, void* act, const std::vector<AdaJob>& jobs,
                      hipStream_t st) {
   const size_t E = s->dtype == DIT_BF16 ? 2 : 4;
-  if (s->dtype == DIT_BF16)
+  const bool fused = adaln_fused((int)jobs.size(), s->batch, s->hidden, s->dtype);
+  if (!fused)
     HIP_TRY(timed(DIT_K_OTHER, 0, 0, st, [&]() { return launch_silu_bf16(s->batch, s->hidden, cond, act, st); }));
   for (size_t j0 = 0; j0 < jobs.size(); j0 += ADA_MAX_ENTRIES) {
     AdaArgs a{};
@@ -651,7 +652,6 @@ dit_status run_adaln(const dit_shape* s, const float* cond, void* act, const std
     a.act = act;
     a.B = s->batch;
     a.D = s->hidden;
-    int wg = 0;
     double bytes = 0;
     const size_t j1 = j0 + ADA_MAX_ENTRIES < jobs.size() ? j0 + ADA_MAX_ENTRIES : jobs.size();
     for (size_t j = j0; j < j1; ++j) {
@@ -660,14 +660,10 @@ dit_status run_adaln(const dit_shape* s, const float* cond, void* act, const std
       e.bias = jobs[j].bias;
       e.out = jobs[j].out;
       e.N = jobs[j].N;
-      e.wg_begin = wg;
-      const int rows_per_wg = s->dtype == DIT_BF16 ? ADA_ROWS_PER_WG : 128;
-      wg += (jobs[j].N + rows_per_wg - 1) / rows_per_wg;
       bytes += (double)jobs[j].N * s->hidden * E;
     }
-    a.total_wg = wg;
     HIP_TRY(timed(DIT_K_ADALN, 2.0 * bytes / E * s->batch, bytes, st,
-                  [&]() { return launch_adaln(a, s->dtype, st); }));
+                  [&]() { return launch_adaln(a, s->dtype, fused, st); }));
   }
   return DIT_OK;
 }

@@ -7,6 +7,8 @@
 //   * timestep + class conditioning, patch embedding, 2-D sin-cos table.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -87,11 +89,7 @@ hipError_t launch_ln_mod(const LnArgs& a, int dtype, hipStream_t st) {
   return dtype == 1 ? ln_dispatch<bf16_t>(a, st) : ln_dispatch<float>(a, st);
 }
 
-// ---------------------------------------------------------------- adaLN GEMV
-// Workgroup = 4 waves x 8 lane-groups x 4 rows = 128 output rows of one
-// entry.  A lane-group of 8 lanes reads 128 contiguous bytes of each of its
-// 4 weight rows per step; SiLU(c) for up to 8 samples sits in LDS and is
-// reused across the 4 rows.
+// Eight weights of either type as floats.
 template <typename WT> struct W8;
 template <> struct W8<bf16_t> {
   static __device__ __forceinline__ void load(const bf16_t* p, float* w) {
@@ -112,100 +110,32 @@ template <> struct W8<float> {
   }
 };
 
-template <typename WT>
-__global__ __launch_bounds__(256) void adaln_kernel(AdaArgs a) {
-  extern __shared__ float sc[];  // [min(B, 8)][D]
-  const int wg = blockIdx.x;
-  int ei = 0;
-  while (ei + 1 < a.ne && wg >= a.e[ei + 1].wg_begin) ++ei;
-  const AdaEntry& E = a.e[ei];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = lane >> 3, li = lane & 7;
-  const int nbase = (wg - E.wg_begin) * 128 + wave * 32 + grp * 4;
-  const WT* __restrict__ W = (const WT*)E.W;
-  const WT* __restrict__ bias = (const WT*)E.bias;
-  const int D = a.D, nch = D >> 3, N = E.N;
-
-  for (int b0 = 0; b0 < a.B; b0 += 8) {
-    const int nb = min(8, a.B - b0);
-    __syncthreads();
-    for (int i = tid; i < nb * D; i += 256) {
-      const float z = a.cond[(long)b0 * D + i];
-      sc[i] = z / (1.0f + expf(-z));
-    }
-    __syncthreads();
-    float acc[4][8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int bb = 0; bb < 8; ++bb) acc[r][bb] = 0.f;
-    for (int ci = li; ci < nch; ci += 8) {
-      float w[4][8];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int n = nbase + r;
-        if (n < N) W8<WT>::load(W + (long)n * D + ci * 8, w[r]);
-        else
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w[r][e] = 0.f;
-      }
-#pragma unroll
-      for (int bb = 0; bb < 8; ++bb) {
-        if (bb < nb) {
-          const float4 s0 = *(const float4*)&sc[bb * D + ci * 8];
-          const float4 s1 = *(const float4*)&sc[bb * D + ci * 8 + 4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float t = acc[r][bb];
-            t = fmaf(w[r][0], s0.x, t); t = fmaf(w[r][1], s0.y, t);
-            t = fmaf(w[r][2], s0.z, t); t = fmaf(w[r][3], s0.w, t);
-            t = fmaf(w[r][4], s1.x, t); t = fmaf(w[r][5], s1.y, t);
-            t = fmaf(w[r][6], s1.z, t); t = fmaf(w[r][7], s1.w, t);
-            acc[r][bb] = t;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int bb = 0; bb < 8; ++bb) {
-        float t = acc[r][bb];
-        t += __shfl_xor(t, 1, 64);
-        t += __shfl_xor(t, 2, 64);
-        t += __shfl_xor(t, 4, 64);
-        acc[r][bb] = t;
-      }
-    // lane li of the group writes sample b0 + li
-    if (li < nb) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int n = nbase + r;
-        if (n >= N) continue;
-        float val = 0.f;
-#pragma unroll
-        for (int bb = 0; bb < 8; ++bb) val = (bb == li) ? acc[r][bb] : val;
-        E.out[(long)(b0 + li) * N + n] = val + ld_as_float<WT>(bias, n);
-      }
-    }
-  }
-}
-
-// bf16 weights: the same product on v_mfma_f32_16x16x32_bf16 as
-// out^T [N, B] = W [N, K] * SiLU(c)^T [K, B].  A workgroup (4 waves x 4 row
-// tiles of 16) owns 256 rows of one entry; each B fragment feeds the four
-// row tiles.  Both operands are read straight from global memory, 16 bytes
-// per lane (row lane%16, k offset 8*(lane/16)): W streams from HBM once,
-// and the B operand, SiLU(c) in bf16 for 16 samples (computed once by
-// silu_bf16_kernel, zero rows past the batch; at most a few hundred KB),
-// stays in L2; lanes of samples past the batch supply zeros without a load
-// (at batch 1, fifteen of sixteen).  No LDS, so many workgroups share a CU
-// and keep enough weight loads in flight to stream HBM (staging the B
-// operand in LDS held one workgroup per CU at hidden 3072).  Measured:
-// 4.2 TB/s with two row tiles per wave and every lane loading, 4.7-5.2 TB/s
-// like this (a plain streaming read of the same rows: 5.8-6.1).  Batches
-// above 16 loop over 16-sample tiles.  D lanes hold column (sample)
-// lane%16, rows 4*(lane/16) + i.
+// ---------------------------------------------------------------- adaLN GEMV
+// out^T [N, B] = W [N, K] * SiLU(c)^T [K, B] on 16-row MFMA tiles
+// (v_mfma_f32_16x16x32_bf16; for fp32 weights four v_mfma_f32_16x16x4_f32,
+// exact fp32 products).  A step of the k loop takes 64 bytes of each of the 16
+// rows: lane (row r16 = lane % 16, quarter kq = lane / 16) reads the 16 bytes
+// at 16 kq of its row's 64, and the B operand holds the same k positions of
+// sample r16, so the assignment of k to MFMA lanes cancels.
+//
+// Bound by HBM reads of W, i.e. by how many loads are in flight.  A workgroup
+// owns 16 RT rows of one matrix and its four waves take a quarter of k each,
+// added through LDS in wave order; the loads of the next U steps are in
+// flight while the current U are multiplied.  One block's matrix (6912 x 1152)
+// is then 432 workgroups; as 27 workgroups whose waves each walked the whole
+// of k it was a serial chain of loads.  Measured with SiLU's launch, before
+// -> after: that matrix at 1 sample 22.8 -> 7.8 us, the joint block's two
+// (18432 x 3072, 226 MB) 83 -> 57 us, two joint blocks and the final layer at
+// hidden 1536 46 -> 34 us; all 28 of DiT-XL/2 (450 MB) at 8 samples 109 ->
+// 107, at 1 sample 94 -> 86 us.  16 loads in flight per lane instead of 8
+// leave too few waves (28 matrices: 167 us).
+//
+// SiLU(c): FUSED, every workgroup computes it into LDS for up to nbc samples
+// at a time and one launch fewer is needed: right where few workgroups repeat
+// that work (28 matrices at 8 samples: 187 us against 107).  Otherwise (bf16
+// only) it comes from `act`, written once by silu_bf16_kernel and read through
+// L2 with the weights.  Lanes of samples past the batch supply zeros.  D
+// lanes hold sample lane % 16, rows 4 (lane / 16) + i.
 __global__ void silu_bf16_kernel(int B, int D, int rows, const float* cond, bf16_t* act) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long)rows * D) return;
@@ -221,62 +151,144 @@ hipError_t launch_silu_bf16(int B, int D, const float* cond, void* act, hipStrea
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void adaln_mfma_kernel(AdaArgs a) {
-  constexpr int RT = ADA_ROWS_PER_WG / 64;  // row tiles of 16 per wave
-  const int wg = blockIdx.x;
-  int ei = 0;
-  while (ei + 1 < a.ne && wg >= a.e[ei + 1].wg_begin) ++ei;
-  const AdaEntry& E = a.e[ei];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int K = a.D, N = E.N;
-  const int nbase = (wg - E.wg_begin) * ADA_ROWS_PER_WG + wave * (16 * RT);
-  const bf16_t* __restrict__ W = (const bf16_t*)E.W;
-  const bf16_t* __restrict__ bias = (const bf16_t*)E.bias;
-  const bf16_t* __restrict__ act = (const bf16_t*)a.act;
-  const int r16 = lane & 15, kq = lane >> 4;
-  const bf16_t* wr[RT];
-#pragma unroll
-  for (int t = 0; t < RT; ++t) wr[t] = W + (long)min(nbase + 16 * t + r16, N - 1) * K + 8 * kq;
+// Staged sample rows are padded by 16 bytes, which spreads the 16 rows of a
+// fragment read over the LDS banks.
+template <typename WT>
+static constexpr int ada_row_elems(int K) { return K + 16 / (int)sizeof(WT); }
 
-  for (int b0 = 0; b0 < a.B; b0 += 16) {
-    const bool live = b0 + r16 < a.B;  // this lane's sample exists
-    const bf16_t* sp = act + (long)(b0 + r16) * K + 8 * kq;
+template <typename WT, int RT, bool FUSED>
+__global__ __launch_bounds__(256) void adaln_mfma_kernel(AdaArgs a) {
+  constexpr int KE = 64 / sizeof(WT);  // k per step
+  constexpr int LE = 16 / sizeof(WT);  // elements per lane and step
+  constexpr int U = 8 / RT;            // steps per group of loads
+  extern __shared__ __attribute__((aligned(16))) unsigned char ada_smem[];
+  f32x4* const red = (f32x4*)ada_smem;                 // [4 waves][RT][64]
+  WT* const act_s = (WT*)(ada_smem + 4 * RT * 64 * 16);  // FUSED: [nbc][ada_row_elems]
+  // every matrix but the last (the final layer's) has the same row count
+  const int wg = blockIdx.x;
+  const int ei = min(wg / a.wg_per_entry, a.ne - 1);
+  const AdaEntry E = a.e[ei];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = a.D, N = E.N;
+  const int nbase = (wg - E.wg_begin) * (16 * RT);  // N is a multiple of 128
+  const int r16 = lane & 15, kq = lane >> 4;
+  // the wave's k range, in whole 128-byte lines (K is a multiple of 64)
+  const int lines = K * (int)sizeof(WT) / 128;
+  const int s0 = 2 * (lines * wave / 4), s1 = 2 * (lines * (wave + 1) / 4);
+  const WT* wr[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) wr[t] = (const WT*)E.W + (long)(nbase + 16 * t + r16) * K + LE * kq;
+
+  // weight fragments of U steps, and (not fused) SiLU(c) fragments with them
+  u32x4 cur[RT][U], nxt[RT][U], cur_b[U], nxt_b[U];
+  const WT* sp = nullptr;  // the lane's SiLU(c) row
+  bool live = false;       // this lane's sample exists
+  auto load = [&](u32x4 (&w)[RT][U], u32x4 (&b)[U], int s) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < s1) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) w[t][u] = *(const u32x4*)(wr[t] + (s + u) * KE);
+        if (!FUSED) b[u] = live ? *(const u32x4*)(sp + (s + u) * KE) : u32x4{0u, 0u, 0u, 0u};
+      }
+  };
+  const int step_b = FUSED ? a.nbc : 16;
+  const int row_e = ada_row_elems<WT>(K);
+  for (int b0 = 0; b0 < a.B; b0 += step_b) {
+    const int nb = min(step_b, a.B - b0);
+    live = r16 < nb;
+    sp = FUSED ? act_s + r16 * row_e + LE * kq : (const WT*)a.act + (long)(b0 + r16) * K + LE * kq;
+    load(cur, cur_b, s0);
+    if (FUSED) {
+      if (b0) __syncthreads();  // the previous samples' reads are done
+      for (int r = 0; r < nb; ++r)
+        for (int k = tid; k < K; k += 256) {  // cond is only 4-byte aligned
+          const float z = a.cond[(long)(b0 + r) * K + k];
+          if constexpr (sizeof(WT) == 2) act_s[r * row_e + k] = f2bf(silu(z));
+          else act_s[r * row_e + k] = z / (1.0f + expf(-z));
+        }
+      __syncthreads();
+    }
     f32x4 acc[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int k0 = 0; k0 < K; k0 += 32) {
-      const bf16x8 bv = live ? *(const bf16x8*)(sp + k0) : bf16x8{};
+    for (int s = s0; s < s1; s += U) {
+      load(nxt, nxt_b, s + U);
 #pragma unroll
-      for (int t = 0; t < RT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)(wr[t] + k0), bv, acc[t], 0, 0, 0);
-    }
-    const int b = b0 + r16;
-    if (b < a.B) {
+      for (int u = 0; u < U; ++u)
+        if (s + u < s1) {
+          const u32x4 bw = !FUSED ? cur_b[u] : live ? *(const u32x4*)(sp + (s + u) * KE) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int t = 0; t < RT; ++t) {
-        const int n = nbase + 16 * t + 4 * kq;  // N is a multiple of 4
-        if (n >= N) continue;
-        const f32x4 v = acc[t];
-        *(f32x4*)(E.out + (long)b * N + n) =
-            f32x4{v[0] + bf2f(bias[n]), v[1] + bf2f(bias[n + 1]), v[2] + bf2f(bias[n + 2]), v[3] + bf2f(bias[n + 3])};
+          for (int t = 0; t < RT; ++t) {
+            if constexpr (sizeof(WT) == 2) {
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur[t][u]),
+                                                               __builtin_bit_cast(bf16x8, bw), acc[t], 0, 0, 0);
+            } else {
+              const f32x4 wf = __builtin_bit_cast(f32x4, cur[t][u]), bf = __builtin_bit_cast(f32x4, bw);
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], bf[e], acc[t], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) cur[t][u] = nxt[t][u];
+        cur_b[u] = nxt_b[u];
       }
+    }
+    if (b0) __syncthreads();  // the previous samples' sums have been read
+#pragma unroll
+    for (int t = 0; t < RT; ++t) red[(wave * RT + t) * 64 + lane] = acc[t];
+    __syncthreads();
+    if (wave < RT && live) {  // wave t adds row tile t
+      f32x4 v = red[wave * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v += red[(w * RT + wave) * 64 + lane];
+      const int n = nbase + 16 * wave + 4 * kq;
+      const WT* bias = (const WT*)E.bias + n;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += ld_as_float<WT>(bias, i);
+      *(f32x4*)(E.out + (long)(b0 + r16) * N + n) = v;
     }
   }
 }
 
-hipError_t launch_adaln(const AdaArgs& a, int dtype, hipStream_t st) {
-  dim3 grid(a.total_wg), block(256);
-  if (dtype == 1) {
-    hipLaunchKernelGGL(adaln_mfma_kernel, grid, block, 0, st, a);
-  } else {
-    const size_t lds = (size_t)(a.B < 8 ? a.B : 8) * a.D * sizeof(float);
-    hipError_t e = hipFuncSetAttribute((const void*)adaln_kernel<float>,
+// Whether the workgroups compute SiLU(c) themselves: always for fp32; for
+// bf16 where matrices x samples is small (one joint block at 8 samples, a few
+// blocks at one or two) and the staged samples take at most 48 KB (three
+// workgroups per CU).  Two joint blocks and the final layer at 2 samples: 34 us
+// against 33.6 + 4.8 for the two launches; 28 matrices at 1 sample 94 us against 84 + 2.4.
+bool adaln_fused(int entries, int B, int D, int dtype) {
+  const int nb = std::min(B, 16);
+  return dtype != 1 || (entries * nb <= 16 && nb * ada_row_elems<bf16_t>(D) * 2 <= 48 * 1024);
+}
+
+template <typename WT, int RT, bool FUSED>
+static hipError_t adaln_launch_t(AdaArgs& a, hipStream_t st) {
+  int wg = 0;
+  for (int j = 0; j < a.ne; ++j) {
+    a.e[j].wg_begin = wg;
+    wg += a.e[j].N / (16 * RT);
+  }
+  a.wg_per_entry = a.e[0].N / (16 * RT);
+  const int row_bytes = ada_row_elems<WT>(a.D) * (int)sizeof(WT);
+  // samples staged per pass: what 64 KB hold
+  a.nbc = std::min(std::min(a.B, 16), std::max(1, 64 * 1024 / row_bytes));
+  const size_t lds = 4 * RT * 64 * 16 + (FUSED ? (size_t)a.nbc * row_bytes : 0);
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)adaln_mfma_kernel<WT, RT, FUSED>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((adaln_kernel<float>), grid, block, lds, st, a);
   }
+  hipLaunchKernelGGL((adaln_mfma_kernel<WT, RT, FUSED>), dim3(wg), dim3(256), lds, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st) {
+  if (dtype != 1) return adaln_launch_t<float, 1, true>(a, st);
+  return fused ? adaln_launch_t<bf16_t, 1, true>(a, st) : adaln_launch_t<bf16_t, 2, false>(a, st);
 }
 
 // ---------------------------------------------------------------- conditioning

@@ -106,18 +106,18 @@ struct LnArgs {
 
 // ------------------------------------------------------------------ adaLN GEMV
 constexpr int ADA_MAX_ENTRIES = 64;
-constexpr int ADA_ROWS_PER_WG = 256;  // bf16 MFMA kernel: output rows per workgroup (the fp32 kernel: 128)
 struct AdaEntry {
   const void* W;     // [N, D]
   const void* bias;  // [N]
   float* out;        // [B, N]
-  int N, wg_begin;
+  int N, wg_begin;   // wg_begin: set by the launcher
 };
 struct AdaArgs {
-  AdaEntry e[ADA_MAX_ENTRIES];
-  int ne, total_wg;
+  AdaEntry e[ADA_MAX_ENTRIES];  // N the same in all but the last, multiples of 128
+  int ne;
+  int wg_per_entry, nbc;  // set by the launcher: workgroups of entry 0, samples staged per pass
   const float* cond;  // [B, D]
-  const void* act;    // bf16 path: SiLU(cond) as bf16 [round16(B), D], zero rows past B
+  const void* act;    // not fused: SiLU(cond) as bf16 [round16(B), D], zero rows past B
   int B, D;
 };
 
@@ -136,7 +136,10 @@ hipError_t launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t st);
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t st);
 hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, hipStream_t st);
 hipError_t launch_ln_mod(const LnArgs& a, int dtype, hipStream_t st);
-hipError_t launch_adaln(const AdaArgs& a, int dtype, hipStream_t st);
+// fused: the kernel computes SiLU(cond) itself (adaln_fused says when), else
+// it reads a.act, written by launch_silu_bf16 before.
+bool adaln_fused(int entries, int B, int D, int dtype);
+hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st);
 // act[r][k] = bf16(SiLU(cond[r][k])) for r < B, 0 for B <= r < round16(B)
 hipError_t launch_silu_bf16(int B, int D, const float* cond, void* act, hipStream_t st);
 hipError_t launch_cond_embed(int B, int D, const float* t, const int32_t* y, const void* w1, const void* b1,
