@@ -643,7 +643,7 @@ struct AdaJob {
 dit_status run_adaln(const dit_shape* s, const float* cond, void* act, const std::vector<AdaJob>& jobs,
                      hipStream_t st) {
   const size_t E = s->dtype == DIT_BF16 ? 2 : 4;
-  const bool fused = adaln_fused((int)jobs.size(), s->batch, s->hidden, s->dtype);
+  const bool fused = adaln_fused((int)jobs.size(), s->batch, s->dtype);
   if (!fused)
     HIP_TRY(timed(DIT_K_OTHER, 0, 0, st, [&]() { return launch_silu_bf16(s->batch, s->hidden, cond, act, st); }));
   for (size_t j0 = 0; j0 < jobs.size(); j0 += ADA_MAX_ENTRIES) {

@@ -122,17 +122,16 @@ template <> struct W8<float> {
 // owns 16 RT rows of one matrix and its four waves take a quarter of k each,
 // added through LDS in wave order; the loads of the next U steps are in
 // flight while the current U are multiplied.  One block's matrix (6912 x 1152)
-// is then 432 workgroups; as 27 workgroups whose waves each walked the whole
-// of k it was a serial chain of loads.  Measured with SiLU's launch, before
-// -> after: that matrix at 1 sample 22.8 -> 7.8 us, the joint block's two
-// (18432 x 3072, 226 MB) 83 -> 57 us, two joint blocks and the final layer at
-// hidden 1536 46 -> 34 us; all 28 of DiT-XL/2 (450 MB) at 8 samples 109 ->
-// 107, at 1 sample 94 -> 86 us.  16 loads in flight per lane instead of 8
-// leave too few waves (28 matrices: 167 us).
+// is then 216 or 432 workgroups; as 27 workgroups whose waves each walked the
+// whole of k it was a serial chain of loads.  Measured with SiLU's launch,
+// before -> after: that matrix at 1 sample 22.8 -> 7.8 us, at 8 25 -> 10, the
+// joint block's two (18432 x 3072, 226 MB) 83 -> 57 us, one of them at 8
+// samples 77 -> 39 us; all 28 of DiT-XL/2 (450 MB) at 8 samples 109 -> 107, at
+// 1 sample 94 -> 86 us.  16 loads in flight per lane instead of 8 leave too few
+// waves (28 matrices: 167 us).
 //
 // SiLU(c): FUSED, every workgroup computes it into LDS for up to nbc samples
-// at a time and one launch fewer is needed: right where few workgroups repeat
-// that work (28 matrices at 8 samples: 187 us against 107).  Otherwise (bf16
+// at a time and one launch fewer is needed (adaln_fused).  Otherwise (bf16
 // only) it comes from `act`, written once by silu_bf16_kernel and read through
 // L2 with the weights.  Lanes of samples past the batch supply zeros.  D
 // lanes hold sample lane % 16, rows 4 (lane / 16) + i.
@@ -201,11 +200,20 @@ __global__ __launch_bounds__(256) void adaln_mfma_kernel(AdaArgs a) {
     load(cur, cur_b, s0);
     if (FUSED) {
       if (b0) __syncthreads();  // the previous samples' reads are done
-      for (int r = 0; r < nb; ++r)
-        for (int k = tid; k < K; k += 256) {  // cond is only 4-byte aligned
-          const float z = a.cond[(long)(b0 + r) * K + k];
-          if constexpr (sizeof(WT) == 2) act_s[r * row_e + k] = f2bf(silu(z));
-          else act_s[r * row_e + k] = z / (1.0f + expf(-z));
+      // four samples at a time, so that their loads overlap (cond is only
+      // 4-byte aligned)
+      for (int r = 0; r < nb; r += 4)
+#pragma unroll 2
+        for (int k = tid; k < K; k += 256) {
+          float z[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) z[i] = a.cond[(long)(b0 + min(r + i, nb - 1)) * K + k];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (r + i < nb) {
+              if constexpr (sizeof(WT) == 2) act_s[(r + i) * row_e + k] = f2bf(silu(z[i]));
+              else act_s[(r + i) * row_e + k] = z[i] / (1.0f + expf(-z[i]));
+            }
         }
       __syncthreads();
     }
@@ -256,14 +264,12 @@ __global__ __launch_bounds__(256) void adaln_mfma_kernel(AdaArgs a) {
 }
 
 // Whether the workgroups compute SiLU(c) themselves: always for fp32; for
-// bf16 where matrices x samples is small (one joint block at 8 samples, a few
-// blocks at one or two) and the staged samples take at most 48 KB (three
-// workgroups per CU).  Two joint blocks and the final layer at 2 samples: 34 us
-// against 33.6 + 4.8 for the two launches; 28 matrices at 1 sample 94 us against 84 + 2.4.
-bool adaln_fused(int entries, int B, int D, int dtype) {
-  const int nb = std::min(B, 16);
-  return dtype != 1 || (entries * nb <= 16 && nb * ada_row_elems<bf16_t>(D) * 2 <= 48 * 1024);
-}
+// bf16 while matrices x samples is at most 4 (one block at four samples, a
+// joint block at two), where repeating it in every workgroup costs less than
+// a launch.  One 6912 x 1152 matrix at 1, 4, 8, 16 samples: 7.8, 9.5, 13.1,
+// 19.7 us fused against 7.2-7.6 + 2.5 for SiLU's launch; 18432 x 3072 at 1, 4,
+// 7 samples: 29, 37, 54 us against 31-34 + 4.7.
+bool adaln_fused(int entries, int B, int dtype) { return dtype != 1 || entries * std::min(B, 16) <= 4; }
 
 template <typename WT, int RT, bool FUSED>
 static hipError_t adaln_launch_t(AdaArgs& a, hipStream_t st) {

@@ -138,7 +138,7 @@ hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, hipStream_t st);
 hipError_t launch_ln_mod(const LnArgs& a, int dtype, hipStream_t st);
 // fused: the kernel computes SiLU(cond) itself (adaln_fused says when), else
 // it reads a.act, written by launch_silu_bf16 before.
-bool adaln_fused(int entries, int B, int D, int dtype);
+bool adaln_fused(int entries, int B, int dtype);
 hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st);
 // act[r][k] = bf16(SiLU(cond[r][k])) for r < B, 0 for B <= r < round16(B)
 hipError_t launch_silu_bf16(int B, int D, const float* cond, void* act, hipStream_t st);
