@@ -101,6 +101,10 @@ __device__ __forceinline__ int xcd_remap(int i, int n) {
   return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// Orders one wave's LDS accesses across its lanes for the compiler (the
+// hardware already executes a wave's LDS instructions in order).
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // ---------------------------------------------------------------- LDS DMA
 // 32-bit LDS address of a __shared__ object.
 __device__ __forceinline__ unsigned lds_address(const void* p) {

@@ -408,6 +408,38 @@ static int group_height(int tiles_m, int tiles_n, int bm, int bn, int tcfg, doub
   return best < 1 ? 1 : best;
 }
 
+// Tile of the fp32 GEMM and, for one problem with the residual epilogue,
+// its k-ranges (*split, 0: none): the least estimated time
+//   rounds of 256 workgroups x BM BN K / split at 155 TFLOP/s x slope + fixed
+// (+ 5 us for the reduction of a split).  A round is a workgroup per CU: those
+// resident beside it share its matrix pipes.  Slopes and fixed times measured
+// per tile over 256..2048 rows at hidden 384 and 1152 (the estimate is within
+// 8% of all of them); e.g. fc1 at 666 x 4608 x 1152: 96 x 64 is two rounds and
+// 63 us, 64 x 64 (3.1 rounds) 81, 32 x 32 75; QKV at 666 x 3456: 96 x 48 is
+// two rounds and 53 us, the others 60-62; fc2 at 666 x 1152 x 4608: 96 x 64 in
+// two ranges 63 + 5 us, 32 x 32 whole 69, 96 x 64 whole 111.  The partials use
+// the dead q/k/v region, so the workspace does not grow.
+static int f32_plan(const GemmProb* p, int np, int epi, size_t part_cap, int* split) {
+  static const double slope[F32_COUNT] = {1.42, 1.20, 1.17, 1.28}, fixed_us[F32_COUNT] = {4.0, 4.0, 5.0, 6.0};
+  const bool can_split = np == 1 && (epi == EPI_RESID || epi == EPI_RESID2);
+  int best = 0;
+  double best_us = -1.0;
+  *split = 0;
+  for (int cfg = 0; cfg < F32_COUNT; ++cfg) {
+    int bm = 0, bn = 0;
+    gemm_f32_tile_dims(cfg, &bm, &bn);
+    long tiles = 0;
+    for (int i = 0; i < np; ++i) tiles += (long)((p[i].M + bm - 1) / bm) * ((p[i].N + bn - 1) / bn);
+    for (int S = 1; S <= (can_split ? 3 : 1); ++S) {
+      if (S > 1 && ((size_t)S * p[0].M * p[0].N * 4 > part_cap || p[0].K / 32 / S < 8)) break;
+      const double us = tile_rounds(tiles * S) * bm * bn * (double)p[0].K / S * 2.0 / (155e6 / 256) * slope[cfg] +
+                        fixed_us[cfg] + (S > 1 ? 5.0 : 0.0);
+      if (best_us < 0 || us < best_us) best = cfg, best_us = us, *split = S > 1 ? S : 0;
+    }
+  }
+  return best;
+}
+
 hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
   GemmArgs& a = G.a;
   int bm = 64, bn = 64, tcfg = 0, split = 0;
@@ -415,6 +447,9 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
     tcfg = choose_tile(a.p, a.nprob, G.epi, G.part_cap, &split);
     gemm_tile_dims(tcfg, &bm, &bn);
     if (!split) split = row_tail(a, G.epi, bm, bn, G.part_cap);
+  } else {
+    tcfg = f32_plan(a.p, a.nprob, G.epi, G.part_cap, &split);
+    gemm_f32_tile_dims(tcfg, &bm, &bn);
   }
   int tiles = 0;
   for (int i = 0; i < a.nprob; ++i) {
@@ -435,13 +470,13 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
   if (split && sp == 0) tiles *= split;
   a.total_tiles = tiles;
   a.tail = split && sp == 1 ? 1 : 0;
-  if (split) {
+  if (split) {  // fp32: always the only problem
     a.p[sp].ksplit = split;
     a.p[sp].part = G.part;
   }
   if (tiles == 0) return hipSuccess;
   hipError_t e = timed(G.kclass, G.flops, G.bytes, st, [&]() {
-    return dtype == DIT_BF16 ? launch_gemm_bf16(a, G.epi, tcfg, st) : launch_gemm_f32(a, G.epi, st);
+    return dtype == DIT_BF16 ? launch_gemm_bf16(a, G.epi, tcfg, st) : launch_gemm_f32(a, G.epi, tcfg, st);
   });
   if (e != hipSuccess || !split) return e;
   const GemmProb& q = a.p[sp];
@@ -451,7 +486,7 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
       return launch_splitk_gelu_bf16(q.part, split, q.M, q.N, q.bias, q.out, st);
     });
   return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0) + q.N * 2.0, st, [&]() {
-    return launch_splitk_resid(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.rows_per_batch, q.resid, st);
+    return launch_splitk_resid(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.rows_per_batch, q.resid, dtype, st);
   });
 }
 

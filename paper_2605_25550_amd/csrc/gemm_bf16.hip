@@ -57,10 +57,6 @@ struct GemmCfg {
   static_assert(LDS <= 160 * 1024, "LDS per CU");
 };
 
-// Orders one wave's LDS accesses across its lanes for the compiler (the
-// hardware already executes a wave's LDS instructions in order).
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 // Stored position of 16-byte chunk c of slice row r.
 __device__ __forceinline__ int chunk_pos(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
 
@@ -767,8 +763,9 @@ hipError_t launch_splitk_gelu_bf16(const float* part, int S, int M, int N, const
 // Split-K reduction into the fp32 residual: four consecutive outputs per
 // lane; the ranges are added in order, then the bias, then the gated update
 // as in the GEMM's residual epilogue.
+template <typename BT>
 __global__ __launch_bounds__(256) void splitk_resid_kernel(const float* __restrict__ part, int S, long MN, int N,
-                                                           const bf16_t* __restrict__ bias,
+                                                           const BT* __restrict__ bias,
                                                            const float* __restrict__ gate, int gate_stride,
                                                            int rows_per_batch, float* __restrict__ resid) {
   const long e = (blockIdx.x * 256L + threadIdx.x) * 4;
@@ -783,22 +780,34 @@ __global__ __launch_bounds__(256) void splitk_resid_kernel(const float* __restri
   }
   const long m = e / N;
   const int n = (int)(e - m * N), b = (int)(m / rows_per_batch);
-  const u32x2 w = *(const u32x2*)(bias + n);
+  f32x4 bv;
+  if constexpr (sizeof(BT) == 2) {
+    const u32x2 w = *(const u32x2*)(bias + n);
+    bv = f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xFFFF0000u), __uint_as_float(w[1] << 16),
+               __uint_as_float(w[1] & 0xFFFF0000u)};
+  } else {
+    bv = *(const f32x4*)(bias + n);
+  }
   const f32x4 g = *(const f32x4*)(gate + (long)b * gate_stride + n);
   f32x4 x = *(const f32x4*)(resid + e);
-  x[0] += g[0] * (y[0] + __uint_as_float(w[0] << 16));
-  x[1] += g[1] * (y[1] + __uint_as_float(w[0] & 0xFFFF0000u));
-  x[2] += g[2] * (y[2] + __uint_as_float(w[1] << 16));
-  x[3] += g[3] * (y[3] + __uint_as_float(w[1] & 0xFFFF0000u));
+  x[0] += g[0] * (y[0] + bv[0]);
+  x[1] += g[1] * (y[1] + bv[1]);
+  x[2] += g[2] * (y[2] + bv[2]);
+  x[3] += g[3] * (y[3] + bv[3]);
   *(f32x4*)(resid + e) = x;
 }
 
 hipError_t launch_splitk_resid(const float* part, int S, int M, int N, const void* bias, const float* gate,
-                               int gate_stride, int rows_per_batch, float* resid, hipStream_t st) {
+                               int gate_stride, int rows_per_batch, float* resid, int dtype, hipStream_t st) {
   const long MN = (long)M * N;
   if (MN == 0) return hipSuccess;
-  hipLaunchKernelGGL(splitk_resid_kernel, dim3((unsigned)((MN / 4 + 255) / 256)), dim3(256), 0, st, part, S, MN, N,
-                     (const bf16_t*)bias, gate, gate_stride, rows_per_batch, resid);
+  dim3 grid((unsigned)((MN / 4 + 255) / 256)), block(256);
+  if (dtype == 1)
+    hipLaunchKernelGGL((splitk_resid_kernel<bf16_t>), grid, block, 0, st, part, S, MN, N, (const bf16_t*)bias, gate,
+                       gate_stride, rows_per_batch, resid);
+  else
+    hipLaunchKernelGGL((splitk_resid_kernel<float>), grid, block, 0, st, part, S, MN, N, (const float*)bias, gate,
+                       gate_stride, rows_per_batch, resid);
   return hipGetLastError();
 }
 

@@ -21,9 +21,9 @@ def _cfg(dtype, hidden, dh, **kw):
 # adaLN: odd numbers of 128-byte weight lines split over the four waves
 # (hidden 64: one or two lines for four waves), one and several passes of 16
 # samples, the bf16 switch between SiLU computed by the workgroups (matrices x
-# samples <= 16) and read back, fp32 samples beyond one 64 KB staging pass
+# samples <= 4) and read back, fp32 samples beyond one 64 KB staging pass
 # (15 x 1156 floats), joint blocks (two matrices).
-ADA = [("bf16", 64, 64, 1, 0), ("bf16", 192, 64, 3, 0), ("bf16", 192, 64, 8, 2), ("bf16", 320, 64, 9, 3),
+ADA = [("bf16", 64, 64, 1, 0), ("bf16", 192, 64, 4, 0), ("bf16", 192, 64, 5, 0), ("bf16", 320, 64, 2, 3),
        ("bf16", 576, 72, 16, 0), ("bf16", 576, 72, 17, 0), ("bf16", 256, 128, 40, 0), ("f32", 64, 64, 1, 0),
        ("f32", 192, 64, 5, 2), ("f32", 1152, 72, 15, 0), ("f32", 576, 72, 33, 0)]
 
@@ -51,3 +51,30 @@ def test_cond_of_four_byte_alignment():
             torch.cuda.synchronize()
             outs.append(x.cpu())
         assert torch.equal(*outs)
+
+
+# fp32 GEMM tiles (32 x 32, 64 x 64, 96 x 64, 96 x 48, and 96 x 64 in k-ranges
+# with the residual reduction), fewer k-slices than k-groups (hidden 64), odd
+# slice counts per k-group, ragged rows, two problems of different row counts;
+# attention with waves that own no keys, partial 16-query and 32-key groups,
+# and 32 queries per workgroup (from 512 such workgroups on).
+F32 = [(64, 64, 1, 1, 0), (64, 64, 3, 15, 0), (192, 64, 2, 17, 5), (576, 72, 1, 33, 0), (576, 72, 2, 97, 3),
+       (256, 128, 2, 127, 0), (256, 128, 1, 130, 31), (1152, 72, 2, 333, 0), (576, 72, 2, 333, 77),
+       (576, 72, 2, 1030, 0), (1152, 72, 1, 1030, 0), (1024, 128, 2, 1100, 0), (1024, 64, 1, 1041, 0)]
+
+
+@pytest.mark.parametrize("hidden,dh,batch,t,tt", F32)
+def test_f32_edges(hidden, dh, batch, t, tt):
+    # fp32 sums of up to 4 hidden products: sqrt(4608) 2^-24 = 4e-6 of the
+    # largest term for each of two chained products, and the softmax between
+    cfg = _cfg("f32", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=4 * hidden)
+    g = _gpu()
+    w, inp = synth.block_weights(cfg, 0), synth.inputs(cfg)
+    x, c, xt = inp["x"], inp["cond"], inp.get("x_txt")
+    y, yt = g.run_block(cfg, w, x, c, xt)
+    if tt:
+        ry, ryt = O.joint_block(x, xt, c, f64(w["img"]), f64(w["txt"]), cfg.heads, cfg.ln_eps)
+        check("txt", yt, ryt, xt, 2e-5)
+    else:
+        ry = O.dit_block(x, c, f64(w["img"]), cfg.heads, cfg.ln_eps)
+    check("img", y, ry, x, 2e-5)
