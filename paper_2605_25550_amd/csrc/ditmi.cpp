@@ -79,8 +79,8 @@ dit_status check_shape(const dit_shape* s, bool step) {
 }
 
 struct Layout {
-  size_t mod, act, h, q, k, v, o, g, x, feat, h1, total;
-  size_t t, vel, cond, xt;  // sampler loop: timesteps [B], velocity [B,T,P], c [B,D], text states [B,Tt,D]
+  size_t mod, act, h, q, k, v, o, g, x, h1, total;
+  size_t vel, cond, xt;     // sampler loop: velocity [B,T,P], c [B,D], text states [B,Tt,D]
   size_t slot_z[2], slot_y[2], slot_c[2];  // serving: two request slots
   size_t qk;  // q/k row length (elements)
   size_t part, part_cap;  // fp32 partials of split GEMMs: the dead q/k/v region, or a region of its own
@@ -128,7 +128,6 @@ Layout layout(const dit_shape* s, int kind) {
     return o;
   };
   if (kind == DIT_WS_COND) {
-    L.feat = take(B * 256 * 4);
     L.h1 = take(B * D * 4);
     L.total = off;
     return L;
@@ -152,10 +151,8 @@ Layout layout(const dit_shape* s, int kind) {
   }
   L.x = step ? take(B * T * D * 4) : 0;
   if (kind == DIT_WS_SAMPLE || kind == DIT_WS_SERVE) {
-    L.t = take(B * 4);
     L.vel = take(B * T * (size_t)s->patch_out * 4);
     L.cond = take(B * D * 4);
-    L.feat = take(B * 256 * 4);
     L.h1 = take(B * D * 4);
     L.xt = take(B * Tt * D * 4);
   }
@@ -802,11 +799,9 @@ dit_status run_sample_loop(const dit_shape* s, const dit_step_weights* w, const 
     const float* c = cond;
     if (cw) {  // c_i = conditioning at t_i = sigma_i * t_scale (fp32), every sample
       const float t = sigmas[i] * t_scale;
-      HIP_TRY(launch_fill_f32((float*)(ws + L.t), B, t, hs));
       HIP_TRY(timed(DIT_K_OTHER, 0, 0, hs, [&]() {
-        return launch_cond_embed(B, D, (const float*)(ws + L.t), y, cw->w_t1, cw->b_t1, cw->w_t2, cw->b_t2,
-                                 cw->class_table, (float*)(ws + L.feat), (float*)(ws + L.h1), (float*)(ws + L.cond),
-                                 s->dtype, hs);
+        return launch_cond_embed(B, D, nullptr, t, y, cw->w_t1, cw->b_t1, cw->w_t2, cw->b_t2, cw->class_table,
+                                 (float*)(ws + L.h1), (float*)(ws + L.cond), s->dtype, hs);
       }));
       c = (const float*)(ws + L.cond);
     }
@@ -1081,7 +1076,7 @@ dit_status dit_cond_embed(const dit_shape* s, const float* t, const int32_t* y, 
   hipStream_t hs = (hipStream_t)stream;
   char* ws = (char*)workspace;
   HIP_TRY(timed(DIT_K_OTHER, 0, 0, hs, [&]() {
-    return launch_cond_embed(s->batch, s->hidden, t, y, w_t1, b_t1, w_t2, b_t2, class_table, (float*)(ws + L.feat),
+    return launch_cond_embed(s->batch, s->hidden, t, 0.f, y, w_t1, b_t1, w_t2, b_t2, class_table,
                              (float*)(ws + L.h1), cond, s->dtype, hs);
   }));
   return DIT_OK;

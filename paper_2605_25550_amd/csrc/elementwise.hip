@@ -298,85 +298,175 @@ hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------- conditioning
-// feat[b][i] = cos(t_b f_i) (i < 128), sin(t_b f_{i-128}) (i >= 128),
-// f_i = exp(-ln(10000) i / 128); evaluated in double for the large arguments.
-__global__ void timestep_feat_kernel(int B, const float* t, float* feat) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= B * 256) return;
-  const int b = idx >> 8, i = idx & 255;
-  const int fi = i & 127;
-  const double f = exp(-9.210340371976184 * (double)fi / 128.0);  // ln(10000)
-  const double arg = (double)t[b] * f;
-  feat[idx] = (float)(i < 128 ? cos(arg) : sin(arg));
+// e_b = [cos(t_b f_i), sin(t_b f_i)], f_i = exp(-ln(10000) i / 128), i < 128;
+// h1 = SiLU(e W1^T + b1);  cond = h1 W2^T + b2 + class_table[y].  Two
+// dependent launches, each bound by latency (3.3 MB at DiT-XL/2, 8 samples):
+// what counts is that a wave's loads are all in flight at once, that samples
+// are independent chains, and that their inputs sit in LDS.  Measured at 8
+// samples, hidden 1152: three launches (features,
+// and each layer a wave per row with a serial loop over the samples) 2.5 + 6.8 +
+// 11.6 us, now 5.3 + 5.9; 16 samples 34.5 -> 18 us, 11 samples at hidden 3072 in
+// fp32 42 -> 29 us
+//
+// Sum over the wavefront of v[i], i < NV (independent chains).
+template <int NV>
+__device__ __forceinline__ void wave_sums(float (&v)[NV]) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_move<0xB1>(v[i]);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_move<0x4E>(v[i]);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_move<0x141>(v[i]);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_move<0x140>(v[i]);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int b = __float_as_int(v[i]);
+    v[i] = (__int_as_float(__builtin_amdgcn_readlane(b, 0)) + __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+           (__int_as_float(__builtin_amdgcn_readlane(b, 32)) + __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+  }
 }
 
-// out[b][n] = post(sum_k W[n][k] in[b][k] + bias[n]); one wavefront per row n.
-// The row is loaded once into registers (8 consecutive weights per lane and
-// chunk, 16-byte loads) and dotted with every sample's input vector.
-// MODE 0: post = SiLU.  MODE 1: post = identity, plus class_table[y[b]][n].
-// K is a multiple of 8 and at most 8 * 64 * RD_MAXCH.
-constexpr int RD_MAXCH = 8;
-template <typename WT, int MODE>
-__global__ __launch_bounds__(256) void rowdot_kernel(int B, int N, int K, const float* in, const WT* W,
-                                                     const WT* bias, const WT* table, const int32_t* y,
-                                                     float* out) {
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (n >= N) return;
-  const int nch = K >> 3;
-  float w[RD_MAXCH][8];
+// Four consecutive weights of either type as floats.
+__device__ __forceinline__ f32x4 ld_w4(const float* p) { return *(const f32x4*)p; }
+__device__ __forceinline__ f32x4 ld_w4(const bf16_t* p) {
+  const u32x2 w = *(const u32x2*)p;
+  return f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xFFFF0000u), __uint_as_float(w[1] << 16),
+               __uint_as_float(w[1] & 0xFFFF0000u)};
+}
+__device__ __forceinline__ float dot4(const f32x4& a, const f32x4& b, float acc) {
+  return fmaf(a[3], b[3], fmaf(a[2], b[2], fmaf(a[1], b[1], fmaf(a[0], b[0], acc))));
+}
+
+// Hidden layer: 16 waves, one row of W1 each; the features of up to CND_NB
+// samples at a time are computed by every workgroup (in double, for the large
+// arguments; one or two per thread) rather than by a launch of their own.
+// t = NULL: every sample at t_val.  N is a multiple of 64.
+constexpr int CND_NB = 16;
+template <typename WT>
+__global__ __launch_bounds__(1024) void cond_hidden_kernel(int B, int N, const float* t, float t_val, const WT* W,
+                                                           const WT* bias, float* h1) {
+  __shared__ __attribute__((aligned(16))) float feat[CND_NB][256];
+  const int tid = threadIdx.x, lane = tid & 63, n = blockIdx.x * 16 + (tid >> 6);
+  const f32x4 w = ld_w4(W + (long)n * 256 + lane * 4);
+  const float bn = ld_as_float<WT>(bias, n);
+  const double f = exp(-9.210340371976184 * (double)(tid & 127) / 128.0);  // ln(10000)
+  for (int b0 = 0; b0 < B; b0 += CND_NB) {
+    const int nb = min(CND_NB, B - b0);
+    if (b0) __syncthreads();  // the previous samples' reads are done
+    for (int b = tid >> 7; b < nb; b += 8) {
+      double sn, cs;
+      sincos((double)(t ? t[b0 + b] : t_val) * f, &sn, &cs);
+      feat[b][tid & 127] = (float)cs;
+      feat[b][128 + (tid & 127)] = (float)sn;
+    }
+    __syncthreads();
+    for (int b = 0; b < nb; b += 4) {
+      float acc[4];
 #pragma unroll
-  for (int i = 0; i < RD_MAXCH; ++i) {
-    const int c = lane + 64 * i;
-    if (c < nch) W8<WT>::load(W + (long)n * K + c * 8, w[i]);
-    else
+      for (int i = 0; i < 4; ++i) acc[i] = dot4(w, *(const f32x4*)&feat[min(b + i, nb - 1)][lane * 4], 0.f);
+      wave_sums(acc);
+      const float z = (lane == 0 ? acc[0] : lane == 1 ? acc[1] : lane == 2 ? acc[2] : acc[3]) + bn;
+      if (lane < 4 && b + lane < nb) h1[(long)(b0 + b + lane) * N + n] = z / (1.0f + expf(-z));
+    }
+  }
+}
+
+// Output layer: NW waves, one row of W2 each, held in registers (G groups of
+// 4 E consecutive weights per lane, 256 E apart).  NS = 4: h1 of up to nbc
+// samples at a time staged in LDS, four samples per pass, E = 1 (conflict-free
+// reads); NS = 1 (one sample): read straight from global memory with the
+// weights, E = 2 (16-byte loads of bf16 weights).
+template <typename WT, int G, int E, int NW, int NS>
+__global__ __launch_bounds__(NW * 64) void cond_out_kernel(int B, int N, int K, int nbc, const float* h1, const WT* W,
+                                                           const WT* bias, const WT* table, const int32_t* y,
+                                                           float* cond) {
+  extern __shared__ __attribute__((aligned(16))) float hs[];  // NS = 4: [nbc][K]
+  const int tid = threadIdx.x, lane = tid & 63, n = blockIdx.x * NW + (tid >> 6);
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 w[G][E];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) w[i][e] = 0.f;
+  for (int g = 0; g < G; ++g) {
+    const int k = (256 * g + lane * 4) * E;
+    if (E == 2) {
+      float t[8] = {};
+      if (k < K) W8<WT>::load(W + (long)n * K + k, t);
+#pragma unroll
+      for (int e = 0; e < E; ++e) w[g][e] = f32x4{t[4 * e], t[4 * e + 1], t[4 * e + 2], t[4 * e + 3]};
+    } else {
+      w[g][0] = k < K ? ld_w4(W + (long)n * K + k) : zero;
+    }
   }
   const float bn = ld_as_float<WT>(bias, n);
-  for (int b = 0; b < B; ++b) {
-    const float* xb = in + (long)b * K;
-    float acc = 0.f;
-#pragma unroll
-    for (int i = 0; i < RD_MAXCH; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nch) {
-        const float4 x0 = *(const float4*)(xb + c * 8), x1 = *(const float4*)(xb + c * 8 + 4);
-        acc = fmaf(w[i][0], x0.x, acc); acc = fmaf(w[i][1], x0.y, acc);
-        acc = fmaf(w[i][2], x0.z, acc); acc = fmaf(w[i][3], x0.w, acc);
-        acc = fmaf(w[i][4], x1.x, acc); acc = fmaf(w[i][5], x1.y, acc);
-        acc = fmaf(w[i][6], x1.z, acc); acc = fmaf(w[i][7], x1.w, acc);
-      }
+  for (int b0 = 0; b0 < B; b0 += nbc) {
+    const int nb = min(nbc, B - b0);
+    // lane i: class embedding of sample b0 + i
+    const float emb = lane < nb ? ld_as_float<WT>(table, (long)y[b0 + lane] * N + n) : 0.f;
+    if (NS > 1) {
+      if (b0) __syncthreads();  // the previous samples' reads are done
+#pragma unroll 4
+      for (int i = tid; i < nb * K / 4; i += NW * 64) ((f32x4*)hs)[i] = ((const f32x4*)(h1 + (long)b0 * K))[i];
+      __syncthreads();
     }
-    acc = wave_sum(acc) + bn;
-    if (lane == 0) {
-      if (MODE == 0) out[(long)b * N + n] = acc / (1.0f + expf(-acc));
-      else out[(long)b * N + n] = acc + ld_as_float<WT>(table, (long)y[b] * N + n);
+    const float* const in = NS > 1 ? hs : h1;
+    for (int b = 0; b < nb; b += NS) {
+      float acc[NS] = {};
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int k = min((256 * g + lane * 4) * E, K - 4 * E);  // past the end the weights are zero
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            acc[i] = dot4(w[g][e], *(const f32x4*)&in[min(b + i, nb - 1) * K + k + 4 * e], acc[i]);
+      }
+      wave_sums(acc);
+      float v = acc[0];
+#pragma unroll
+      for (int i = 1; i < NS; ++i) v = lane - b == i ? acc[i] : v;
+      if (lane >= b && lane < b + NS && lane < nb) cond[(long)(b0 + lane) * N + n] = v + bn + emb;
     }
   }
 }
 
-hipError_t launch_cond_embed(int B, int D, const float* t, const int32_t* y, const void* w1, const void* b1,
-                             const void* w2, const void* b2, const void* table, float* feat, float* h1,
-                             float* cond, int dtype, hipStream_t st) {
-  hipLaunchKernelGGL(timestep_feat_kernel, dim3((B * 256 + 255) / 256), dim3(256), 0, st, B, t, feat);
+template <typename WT>
+static hipError_t cond_launch_t(int B, int D, const float* t, float t_val, const int32_t* y, const WT* w1,
+                                const WT* b1, const WT* w2, const WT* b2, const WT* table, float* h1, float* cond,
+                                hipStream_t st) {
+  hipLaunchKernelGGL((cond_hidden_kernel<WT>), dim3(D / 16), dim3(1024), 0, st, B, D, t, t_val, w1, b1, h1);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid((D + 3) / 4), block(256);
-  if (dtype == 1) {
-    hipLaunchKernelGGL((rowdot_kernel<bf16_t, 0>), grid, block, 0, st, B, D, 256, feat, (const bf16_t*)w1,
-                       (const bf16_t*)b1, (const bf16_t*)nullptr, (const int32_t*)nullptr, h1);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((rowdot_kernel<bf16_t, 1>), grid, block, 0, st, B, D, D, h1, (const bf16_t*)w2,
-                       (const bf16_t*)b2, (const bf16_t*)table, y, cond);
+  // h1 of as many samples as 64 KB hold (at least 4: hidden <= 4096), one lane
+  // each at most.  4 rows per workgroup fill the GPU soonest; 16 where staging
+  // the samples for every 4 rows would be the larger part of the work (11
+  // samples at hidden 3072, fp32: 34 us with 4 rows, 23 with 16).
+  const int nbc = std::min(std::min(B, 64), 64 * 1024 / (D * 4));
+  const size_t lds = B > 1 ? (size_t)nbc * D * 4 : 0;
+#define COND_OUT(G, E, NW, NS)                                                                                       \
+  hipLaunchKernelGGL((cond_out_kernel<WT, G, E, NW, NS>), dim3(D / NW), dim3(NW * 64), lds, st, B, D, D, nbc, h1, w2, \
+                     b2, table, y, cond)
+  const bool wide = (size_t)B * D * 4 > 40 * 1024;
+  if (D <= 1280) {  // 5 x 256 weights per row
+    if (B == 1) COND_OUT(3, 2, 4, 1);
+    else if (wide) COND_OUT(5, 1, 16, 4);
+    else COND_OUT(5, 1, 4, 4);
   } else {
-    hipLaunchKernelGGL((rowdot_kernel<float, 0>), grid, block, 0, st, B, D, 256, feat, (const float*)w1,
-                       (const float*)b1, (const float*)nullptr, (const int32_t*)nullptr, h1);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((rowdot_kernel<float, 1>), grid, block, 0, st, B, D, D, h1, (const float*)w2,
-                       (const float*)b2, (const float*)table, y, cond);
+    if (B == 1) COND_OUT(8, 2, 4, 1);
+    else if (wide) COND_OUT(16, 1, 16, 4);
+    else COND_OUT(16, 1, 4, 4);
   }
+#undef COND_OUT
   return hipGetLastError();
+}
+
+hipError_t launch_cond_embed(int B, int D, const float* t, float t_val, const int32_t* y, const void* w1,
+                             const void* b1, const void* w2, const void* b2, const void* table, float* h1,
+                             float* cond, int dtype, hipStream_t st) {
+  if (dtype == 1)
+    return cond_launch_t(B, D, t, t_val, y, (const bf16_t*)w1, (const bf16_t*)b1, (const bf16_t*)w2,
+                         (const bf16_t*)b2, (const bf16_t*)table, h1, cond, st);
+  return cond_launch_t(B, D, t, t_val, y, (const float*)w1, (const float*)b1, (const float*)w2, (const float*)b2,
+                       (const float*)table, h1, cond, st);
 }
 
 // Patch embedding x = z W^T + b (+ pos), fp32 accumulation in the order
@@ -514,19 +604,6 @@ hipError_t launch_pos_embed_2d(int gh, int gw, int D, float* pos, hipStream_t st
 }
 
 // ---------------------------------------------------------------- sampler loop
-// p[i] = v for i < n (per-step timestep for the conditioning; a kernel, not a
-// memset, so that the loop can be captured into a HIP graph).
-__global__ void fill_f32_kernel(float* p, int n, float v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-hipError_t launch_fill_f32(float* p, int n, float v, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_f32_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
-  return hipGetLastError();
-}
-
 // Euler update z += a * v over n floats (n a multiple of 4, 16-byte aligned).
 __global__ void axpy_f32_kernel(f32x4* z, const f32x4* v, float a, long n4) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;

@@ -142,13 +142,13 @@ bool adaln_fused(int entries, int B, int dtype);
 hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st);
 // act[r][k] = bf16(SiLU(cond[r][k])) for r < B, 0 for B <= r < round16(B)
 hipError_t launch_silu_bf16(int B, int D, const float* cond, void* act, hipStream_t st);
-hipError_t launch_cond_embed(int B, int D, const float* t, const int32_t* y, const void* w1, const void* b1,
-                             const void* w2, const void* b2, const void* table, float* feat, float* h1,
+// t: [B] timesteps, or NULL for t_val in every sample; h1: [B, D] scratch
+hipError_t launch_cond_embed(int B, int D, const float* t, float t_val, const int32_t* y, const void* w1,
+                             const void* b1, const void* w2, const void* b2, const void* table, float* h1,
                              float* cond, int dtype, hipStream_t st);
 hipError_t launch_patch_embed(int rows, int T, int P, int D, const float* z, const void* w, const void* b,
                               const float* pos, float* x, int dtype, hipStream_t st);
 hipError_t launch_pos_embed_2d(int gh, int gw, int D, float* pos, hipStream_t st);
-hipError_t launch_fill_f32(float* p, int n, float v, hipStream_t st);
 // z[i] += a * v[i], i < n; n a multiple of 4, both 16-byte aligned
 hipError_t launch_axpy_f32(float* z, const float* v, float a, long n, hipStream_t st);
 

@@ -78,3 +78,28 @@ def test_f32_edges(hidden, dh, batch, t, tt):
     else:
         ry = O.dit_block(x, c, f64(w["img"]), cfg.heads, cfg.ln_eps)
     check("img", y, ry, x, 2e-5)
+
+
+# Conditioning: one and several groups of four samples, more samples than one
+# staging pass holds (16 for the features; 64 KB of hidden states: 42 at hidden
+# 384, 4 at 4096), both register sizes of the output layer's rows (hidden up
+# to 1280 and above), a last group of 256 columns that is not full.
+@pytest.mark.parametrize("dtype,hidden,dh,batch", [("bf16", 64, 64, 1), ("bf16", 1152, 72, 5), ("bf16", 384, 64, 45),
+                                                   ("bf16", 1344, 64, 17), ("bf16", 4096, 128, 6), ("f32", 1280, 64, 13),
+                                                   ("f32", 1152, 72, 33)])
+def test_cond_embed_edges(dtype, hidden, dh, batch):
+    import paper_2605_25550_amd as dm
+    g = _gpu()
+    cfg = synth.CONFIGS["c1"].with_(dtype=dtype, hidden=hidden, heads=hidden // dh, head_dim=dh, batch=batch, tokens=1,
+                                    n_blocks=1, n_classes=30, mlp_hidden=64)
+    sw = {k: v for k, v in synth.step_weights(cfg).items()}
+    t = np.linspace(0.0, 999.0, batch).astype(np.float32)
+    y = (np.arange(batch) * 7 % 30).astype(np.int32)
+    shape = dm.shape_of(cfg)
+    w = {k: g.dev(sw[k], dm.weight_dtype(shape)) for k in ("w_t1", "b_t1", "w_t2", "b_t2", "class_table")}
+    out = torch.full((batch, hidden), float("nan"), device="cuda")
+    dm.cond_embed(shape, g.dev(t), g.dev(y, torch.int32), w, out, dm.alloc_workspace(shape, dm.DIT_WS_COND))
+    torch.cuda.synchronize()
+    ref = O.class_conditioning(t.astype(np.float64), y, **f64({k: sw[k] for k in w}))
+    # fp32 arithmetic for both weight types: two chained sums of up to 4096 products
+    check("cond", g.host(out), ref, None, 4e-6)
