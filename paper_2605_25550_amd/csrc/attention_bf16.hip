@@ -761,6 +761,160 @@ __global__ __launch_bounds__(NW * 64, WPC) void attn_bf16_pipe_kernel(AttnArgs a
   }
 }
 
+// Small grids: 32 queries per workgroup, the keys split over its four waves
+// (wave w takes the 64-key tiles w, w + 4, ... with a softmax state of its
+// own), the four states merged through LDS.  One sample of 256 tokens is then
+// 128 workgroups whose waves handle one key tile each, instead of 32
+// workgroups that walk four.  K and V^T fragments come straight from global
+// memory (L2) as 16-byte loads in the MFMAs' layout: no two waves of a
+// workgroup read the same key, so staging them in LDS would share nothing;
+// the next tile's K is requested as soon as this one's is used up, V^T before
+// the scores.  Orientation and key order as above.  Bound by latency: launch,
+// one round of loads, one tile, the merge; DiT-XL/2 at 256 tokens x 1 9.0 -> 5.7 us,
+// 512 x 1 13.4 -> 7.2.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_bf16_split_kernel(AttnArgs a) {
+  using C = AttnCfg<DH>;
+  constexpr int OS = DH + 4;  // row stride of a wave's O in LDS
+  __shared__ __attribute__((aligned(16))) float os[4][32][OS];
+  __shared__ float ml[4][2][32];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r32 = lane & 31;
+  const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 32;
+  const int Tj = a.Tj, Tjp = a.Tj_pad;
+  const long bh = (long)b * a.H + h;
+  const bf16_t* __restrict__ qp = (const bf16_t*)a.q + bh * Tj * C::DHP;
+  const bf16_t* __restrict__ kp = (const bf16_t*)a.k + bh * Tj * C::DHP;
+  const bf16_t* __restrict__ vp = (const bf16_t*)a.v + bh * DH * (long)Tjp;
+
+  bf16x8 qf[C::KS], kf[2][C::KS];
+  const bf16_t* const qr = qp + (long)min(q0 + r32, Tj - 1) * C::DHP + g * 8;
+#pragma unroll
+  for (int s = 0; s < C::KS; ++s) qf[s] = *(const bf16x8*)(qr + s * 16);
+  auto load_k = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      const bf16_t* kr = kp + (long)min(tile * 64 + kt * 32 + r32, Tj - 1) * C::DHP + g * 8;  // past the end: masked
+#pragma unroll
+      for (int s = 0; s < C::KS; ++s) kf[kt][s] = *(const bf16x8*)(kr + s * 16);
+    }
+  };
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x16 oacc[C::DT];
+#pragma unroll
+  for (int t = 0; t < C::DT; ++t) oacc[t] = f32x16{};
+
+  const int nkv = (Tj + 63) / 64;
+  if (wave < nkv) load_k(wave);
+  for (int tile = wave; tile < nkv; tile += 4) {
+    const int kv0 = tile * 64;
+    // V^T chunk 2c + g of row 32 t + r32 (rows past head_dim feed unused O rows)
+    u32x4 vf[C::DT][4];
+#pragma unroll
+    for (int t = 0; t < C::DT; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        vf[t][c] = *(const u32x4*)(vp + (long)min(32 * t + r32, DH - 1) * Tjp + min(kv0 + 16 * c + 8 * g, Tjp - 8));
+    f32x16 s[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+    for (int st = 0; st < C::KS; ++st)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+        s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt][st], qf[st], s[kt], 0, 0, 0);
+    if (tile + 4 < nkv) load_k(tile + 4);
+    if (kv0 + 64 > Tj) {
+      // keys past the end: scores -inf, and their V^T columns (stale or
+      // clamped) zero, so that zero probabilities cannot meet a NaN; element i
+      // of chunk 2c + g is key 16 c + 4 g + i, i < 4, and 16 c + 4 g + 4 + i after
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (kv0 + kt * 32 + (e >> 2) * 8 + g * 4 + (e & 3) >= Tj) s[kt][e] = -INFINITY;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int key = kv0 + 16 * c + 4 * g + 2 * w + (w >= 2 ? 4 : 0);
+          const unsigned mask = key + 1 < Tj ? 0xFFFFFFFFu : key < Tj ? 0xFFFFu : 0u;
+#pragma unroll
+          for (int t = 0; t < C::DT; ++t) vf[t][c][w] &= mask;
+        }
+    }
+    float m = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) m = fmaxf(m, s[kt][e]);
+    const float m_new = fmaxf(m_run, max_halves(m));
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    m_run = m_new;
+    float lsum = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        s[kt][e] = __builtin_amdgcn_exp2f(s[kt][e] - m_new);
+        lsum += s[kt][e];
+      }
+    l_run = l_run * alpha + lsum;
+    if (tile != wave)
+#pragma unroll
+      for (int t = 0; t < C::DT; ++t) oacc[t] *= alpha;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int kt = c >> 1, e0 = (c & 1) * 8;
+      const u32x4 pw = {pack_bf16x2(s[kt][e0], s[kt][e0 + 1]), pack_bf16x2(s[kt][e0 + 2], s[kt][e0 + 3]),
+                        pack_bf16x2(s[kt][e0 + 4], s[kt][e0 + 5]), pack_bf16x2(s[kt][e0 + 6], s[kt][e0 + 7])};
+#pragma unroll
+      for (int t = 0; t < C::DT; ++t)
+        oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[t][c]),
+                                                          __builtin_bit_cast(bf16x8, pw), oacc[t], 0, 0, 0);
+    }
+  }
+
+  // merge: with m = max_w m_w and f_w = 2^(m_w - m), O = sum_w f_w O_w /
+  // sum_w f_w l_w (a wave without keys has m = -inf and l = O = 0)
+  const float l_tot = sum_halves(l_run);
+  if (g == 0) {
+    ml[wave][0][r32] = m_run;
+    ml[wave][1][r32] = l_tot;
+  }
+#pragma unroll
+  for (int t = 0; t < C::DT; ++t)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int d = t * 32 + jj * 8 + g * 4;
+      if (d < DH)
+        *(f32x4*)&os[wave][r32][d] =
+            f32x4{oacc[t][jj * 4], oacc[t][jj * 4 + 1], oacc[t][jj * 4 + 2], oacc[t][jj * 4 + 3]};
+    }
+  __syncthreads();
+  constexpr int G4 = DH / 4;  // 4-column groups per query
+  for (int i = tid; i < 32 * G4; i += 256) {
+    const int qr_ = i / G4, d = (i - qr_ * G4) * 4, qi = q0 + qr_;
+    if (qi >= Tj) continue;
+    float m = ml[0][0][qr_];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) m = fmaxf(m, ml[w][0][qr_]);
+    float den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = __builtin_amdgcn_exp2f(ml[w][0][qr_] - m);
+      den += f * ml[w][1][qr_];
+      num += f * *(const f32x4*)&os[w][qr_][d];
+    }
+    const float inv = 1.0f / den;
+    const long orow = qi < a.T_img ? (long)b * a.T_img + qi
+                                   : (long)a.B * a.T_img + (long)b * a.T_txt + (qi - a.T_img);
+    *(u32x2*)((bf16_t*)a.o + orow * a.D + h * DH + d) =
+        u32x2{pack_bf16x2(num[0] * inv, num[1] * inv), pack_bf16x2(num[2] * inv, num[3] * inv)};
+  }
+}
+
 // Merge of the units of the split items: per query, with m = max_s m_s and
 // f_s = 2^(m_s - m),  O = sum_s f_s O_s / sum_s f_s l_s  (ranges in order
 // s = 0, 1, ...), stored as the o row of the query in bf16.  One lane per
@@ -833,14 +987,26 @@ size_t attn_split_plan(int B, int H, int Tj, int head_dim, size_t part_cap, int*
 }
 
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t st) {
-  // Enough work items for every CU, or at least half of them with long
-  // sequences (32 key tiles or more, where the steady state dominates, e.g.
-  // 3 heads over 17550 tokens: 207 items): the pipelined kernel, 8 waves x
-  // 32 queries per workgroup.  Otherwise (few, short sequences) the first
-  // kernel with 4 waves x 32 queries, which spreads the work over twice as
-  // many workgroups.
+  // Three kernels by grid and length (us per launch, measured side by side):
+  // - one round of 32-query workgroups, or two where the keys are many and
+  //   head_dim leaves two workgroups per CU room: keys split over the waves (1 x
+  //   16 heads of 72: 256 tokens 5.7 against 9.0 for the four-wave kernel, 512
+  //   7.2 against 13.4, 1024 (512 workgroups) 19.4 against 22.1 for the
+  //   pipelined one; 384 workgroups at 256 tokens 10.4 against 9.0; head_dim 128,
+  //   512 workgroups at 1000 tokens 33.0 against 31.2);
+  // - 256 items of 256 queries, or 64 with at least 6 key tiles, where the
+  //   pipelined loop's steady state counts: 8 waves x 32 queries per workgroup
+  //   (240 items x 1077 tokens of head_dim 64: 27.5 against 39.1 for the
+  //   four-wave kernel; 144 items x 1500 of 128: 53 against 112; 160 x 400 of 72:
+  //   15.4 against 20.4; 96 x 333 of 72: 13.1 against 13.0; 128 x 256: 12.3
+  //   against 11.3);
+  // - else 4 waves x 32 queries, which spreads short sequences over twice as
+  //   many workgroups.
   const long items = (long)((a.Tj + 255) / 256) * a.H * a.B;
-  const bool wide = items >= 256 || (items >= 128 && a.Tj >= 2048);
+  const long wg32 = (long)((a.Tj + 31) / 32) * a.H * a.B;
+  const bool small = wg32 <= (a.Tj >= 384 && head_dim < 128 ? 512 : 256);
+  const bool wide = !small && (items >= 256 || (items >= 64 && a.Tj >= 384));
+  dim3 grid_s((a.Tj + 31) / 32, a.H, a.B);
   const int nw = wide ? 8 : 4;
   dim3 grid((a.Tj + nw * 32 - 1) / (nw * 32), a.H, a.B), block(nw * 64);
   // the pipelined kernel maps a 1-D grid to its items and split units
@@ -858,6 +1024,8 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t st) {
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<DHV, 8>), grid1, block, 0, st, p);                   \
     if (p.n_tail > 0)                                                                             \
       hipLaunchKernelGGL((attn_merge_kernel<DHV, ATTN_PIPE_QUERIES>), grid_m, dim3(256), 0, st, p); \
+  } else if (small) {                                                                             \
+    hipLaunchKernelGGL((attn_bf16_split_kernel<DHV>), grid_s, dim3(256), 0, st, a);                \
   } else {                                                                                        \
     hipLaunchKernelGGL((attn_bf16_dma_kernel<DHV, 4, 1>), grid, block, 0, st, a);                  \
   }
