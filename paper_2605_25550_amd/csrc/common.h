@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace ditmi {
 
 typedef uint16_t bf16_t;  // storage type of bfloat16 in memory
@@ -90,6 +92,32 @@ __device__ __forceinline__ float gelu_tanh(float u) {
 // SiLU z / (1 + exp(-z)) with the hardware reciprocal (within 1 ulp).
 __device__ __forceinline__ float silu(float z) {
   return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
+}
+
+// part[0] + part[stride] + ... + part[(S - 1) stride], S <= MS, added in that
+// order.  Every load is in flight before the first sum: a loop over S would
+// wait for each (ranges past S re-read the last one and are not added).
+template <int MS>
+__device__ __forceinline__ f32x4 sum_parts(const float* part, int S, long stride) {
+  f32x4 p[MS];
+#pragma unroll
+  for (int s = 0; s < MS; ++s) p[s] = *(const f32x4*)(part + min(s, S - 1) * stride);
+  f32x4 y = p[0];
+#pragma unroll
+  for (int s = 1; s < MS; ++s) {
+    const f32x4 t = y + p[s];
+    y = s < S ? t : y;
+  }
+  return y;
+}
+// Calls launch(integral_constant MS) with the MS of {2, 3, 4, 6, 8} next to S.
+template <typename Fn>
+inline void with_max_parts(int S, Fn&& launch) {
+  if (S <= 2) launch(std::integral_constant<int, 2>());
+  else if (S == 3) launch(std::integral_constant<int, 3>());
+  else if (S == 4) launch(std::integral_constant<int, 4>());
+  else if (S <= 6) launch(std::integral_constant<int, 6>());
+  else launch(std::integral_constant<int, 8>());
 }
 
 // Workgroup id -> logical tile id so that consecutive logical tiles land on

@@ -215,6 +215,10 @@ struct Gemm {
   double flops = 0, bytes = 0;
   float* part = nullptr;  // fp32 scratch for a split problem, part_cap bytes
   size_t part_cap = 0;
+  // residual GEMMs: the LayerNorm-modulate that follows, or null.  Where the
+  // whole problem is split, its reduction does it too and ln_done is set.
+  const LnArgs* ln = nullptr;
+  bool ln_done = false;
 };
 
 // bf16 tile choice, from per-shape measurements on MI355X (256 CUs).
@@ -482,6 +486,12 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
     return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 2.0) + q.N * 2.0, st, [&]() {
       return launch_splitk_gelu_bf16(q.part, split, q.M, q.N, q.bias, q.out, st);
     });
+  if (G.ln && G.ln->nseg == 1 && a.nprob == 1) {
+    G.ln_done = true;
+    return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0 + (dtype == DIT_BF16 ? 2.0 : 4.0)), st, [&]() {
+      return launch_splitk_resid_ln(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.resid, *G.ln, dtype, st);
+    });
+  }
   return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0) + q.N * 2.0, st, [&]() {
     return launch_splitk_resid(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.rows_per_batch, q.resid, dtype, st);
   });
@@ -501,7 +511,24 @@ struct StreamIO {
     if (_e != hipSuccess) return fail(DIT_ERR_HIP, "%s: %s", #expr, hipGetErrorString(_e)); \
   } while (0)
 
-dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io, int ns, hipStream_t st) {
+// The LayerNorm-modulate of one stream into the operand buffer h, with the
+// modulation vectors shift and scale (stride between samples).
+LnArgs ln_one(const dit_shape* s, const Layout& L, char* ws, const float* x, int Ts, const float* shift,
+              const float* scale, int stride) {
+  LnArgs a{};
+  a.nseg = 1;
+  a.D = s->hidden;
+  a.eps = s->ln_eps;
+  a.total_rows = s->batch * Ts;
+  a.s[0] = LnSeg{x, ws + L.h, shift, scale, s->batch * Ts, Ts, stride, 0};
+  return a;
+}
+
+// One block.  *ln_done: on entry, whether the LayerNorm that opens it has
+// been done already (by the call before); on return, whether `next`, the
+// LayerNorm after the block (null: none), has.
+dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io, int ns, const LnArgs* next,
+                     bool* ln_done, hipStream_t st) {
   const int B = s->batch, D = s->hidden, F = s->mlp_hidden, H = s->heads, dh = s->head_dim;
   const int dt = s->dtype;
   const size_t E = dt == DIT_BF16 ? 2 : 4;
@@ -512,7 +539,7 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
   // row offsets of stream 1 inside the stream-major activation buffers
   auto act = [&](char* base, int si, long width) { return (void*)(base + (si ? rows0 * width * E : 0)); };
 
-  auto ln = [&](int which) -> hipError_t {  // which 0: (shift1, scale1), 1: (shift2, scale2)
+  auto ln_args = [&](int which) {  // 0: (shift1, scale1), 1: (shift2, scale2)
     LnArgs a{};
     a.nseg = ns;
     a.D = D;
@@ -531,8 +558,10 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
       begin += g.rows;
     }
     a.total_rows = (int)begin;
-    const double bytes = (double)begin * D * (4 + E);
-    return timed(DIT_K_LN_MOD, 0, bytes, st, [&]() { return launch_ln_mod(a, dt, st); });
+    return a;
+  };
+  auto ln = [&](const LnArgs& a) -> hipError_t {
+    return timed(DIT_K_LN_MOD, 0, (double)a.total_rows * D * (4 + E), st, [&]() { return launch_ln_mod(a, dt, st); });
   };
   auto prob_common = [&](GemmProb& p, int i, const void* A, const void* W, const void* bias, int N, int K) {
     p.A = A;
@@ -547,7 +576,7 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
   for (int i = 0; i < ns; ++i) tokens += (double)B * io[i].Ts;
 
   // (1) h = LN(x) * (1 + scale1) + shift1
-  HIP_TRY(ln(0));
+  if (!*ln_done) HIP_TRY(ln(ln_args(0)));
   // (2) q, k, v = h W_qkv^T + b_qkv, scattered head-major
   {
     Gemm G;
@@ -603,8 +632,11 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
     }));
   }
   // (4) x += gate1 * (o W_o^T + b_o)
+  // (5) h = LN(x) * (1 + scale2) + shift2
   {
+    const LnArgs ln2 = ln_args(1);
     Gemm G;
+    G.ln = &ln2;
     G.epi = EPI_RESID;
     G.kclass = DIT_K_GEMM_OUT;
     G.a.nprob = ns;
@@ -622,9 +654,8 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
     G.flops = 2.0 * tokens * D * D;
     G.bytes = (tokens * D + ns * (double)D * D) * E + tokens * D * 8.0;
     HIP_TRY(run_gemm(G, dt, st));
+    if (!G.ln_done) HIP_TRY(ln(ln2));
   }
-  // (5) h = LN(x) * (1 + scale2) + shift2
-  HIP_TRY(ln(1));
   // (6) g = GELU(h W_1^T + b_1)
   {
     Gemm G;
@@ -647,6 +678,7 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
     Gemm G;
     G.epi = EPI_RESID2;
     G.kclass = DIT_K_GEMM_FC2;
+    G.ln = next;
     G.a.nprob = ns;
     for (int i = 0; i < ns; ++i) {
       GemmProb& p = G.a.p[i];
@@ -660,6 +692,7 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
     G.flops = 2.0 * tokens * D * F;
     G.bytes = (tokens * F + ns * (double)D * F) * E + tokens * D * 8.0;
     HIP_TRY(run_gemm(G, dt, st));
+    *ln_done = G.ln_done;
   }
   return DIT_OK;
 }
@@ -748,21 +781,23 @@ dit_status run_step(const dit_shape* s, const dit_step_weights* w, const Layout&
   }));
 
   // (a4-a11) blocks
+  const LnArgs ln_final = ln_one(s, L, ws, x, T, mod_final, mod_final + D, 2 * D);
+  bool ln_done = false;
   for (int l = 0; l < s->n_blocks; ++l) {
     StreamIO io[2] = {{&w->blocks[l].img, x, mod + (size_t)(l * ns) * per, T},
                       {&w->blocks[l].txt, x_txt, mod + (size_t)(l * ns + 1) * per, s->text_tokens}};
-    if ((st = run_block(s, L, ws, io, ns, hs)) != DIT_OK) return st;
+    // the LayerNorm after this block: the next block's first, or the final one
+    const bool last = l + 1 == s->n_blocks;
+    const float* m1 = mod + (size_t)((l + 1) * ns) * per;
+    const LnArgs next = last ? ln_final : ln_one(s, L, ws, x, T, m1, m1 + D, 6 * D);
+    if ((st = run_block(s, L, ws, io, ns, joint ? nullptr : &next, &ln_done, hs)) != DIT_OK) return st;
   }
 
   // (a12) out = (LN(x) * (1 + scale_f) + shift_f) W_final^T + b_final, image tokens only
   {
-    LnArgs a{};
-    a.nseg = 1;
-    a.D = D;
-    a.eps = s->ln_eps;
-    a.total_rows = B * T;
-    a.s[0] = LnSeg{x, ws + L.h, mod_final, mod_final + D, B * T, T, 2 * D, 0};
-    HIP_TRY(timed(DIT_K_LN_MOD, 0, (double)B * T * D * 6.0, hs, [&]() { return launch_ln_mod(a, s->dtype, hs); }));
+    if (!ln_done)
+      HIP_TRY(timed(DIT_K_LN_MOD, 0, (double)B * T * D * 6.0, hs,
+                    [&]() { return launch_ln_mod(ln_final, s->dtype, hs); }));
     Gemm G;
     G.epi = EPI_STORE;
     G.kclass = DIT_K_OTHER;
@@ -843,7 +878,8 @@ dit_status block_call(const dit_shape* s, const dit_block_weights* w, float* x, 
   dit_status st = run_adaln(s, cond, ws + L.act, jobs, hs);
   if (st != DIT_OK) return st;
   StreamIO io[2] = {{&w->img, x, mod, s->tokens}, {&w->txt, x_txt, mod + per, s->text_tokens}};
-  return run_block(s, L, ws, io, joint ? 2 : 1, hs);
+  bool ln_done = false;
+  return run_block(s, L, ws, io, joint ? 2 : 1, nullptr, &ln_done, hs);
 }
 
 // ------------------------------------------------------------------ static scratch

@@ -110,6 +110,99 @@ template <> struct W8<float> {
   }
 };
 
+// ---------------------------------------------------------------- split-K reduction + LayerNorm + modulate
+// The reduction of a split residual GEMM (splitk_resid_kernel) and the
+// LayerNorm-modulate of the rows it updates in one launch: x += gate (sum of
+// the partials + bias), h = LN(x) (1 + scale) + shift.  A workgroup of four
+// waves per row (NV 4-column groups per thread), so that 256 rows still are
+// 256 workgroups; exact two-pass statistics as in ln_mod_kernel.  Bound by
+// latency at the row counts that are split: 256 rows of 1152 in six ranges 5.1 us
+// (6.1 with a loop over the ranges), against 4.2 + 3.8 for the two launches.
+__device__ __forceinline__ float block_sum(float v, float* slot) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (slot[0] + slot[1]) + (slot[2] + slot[3]);
+}
+
+template <typename WT, int NV, int MS>
+__global__ __launch_bounds__(256) void splitk_resid_ln_kernel(const float* __restrict__ part, int S, long MN, int D,
+                                                              const WT* __restrict__ bias,
+                                                              const float* __restrict__ gate, int gate_stride,
+                                                              float* __restrict__ resid, LnSeg seg, float eps) {
+  __shared__ float slots[2][4];
+  const int row = blockIdx.x, tid = threadIdx.x, nq = D >> 2;
+  const int b = row / seg.rows_per_batch;  // uniform
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 v[NV], s4[NV], c4[NV];
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = tid + 256 * i, n = min(c, nq - 1) * 4;  // clamped: always valid
+    const long e = (long)row * D + n;
+    const f32x4 y = sum_parts<MS>(part + e, S, MN);
+    f32x4 bv;
+    if constexpr (sizeof(WT) == 2) {
+      const u32x2 w = *(const u32x2*)(bias + n);
+      bv = f32x4{__uint_as_float(w[0] << 16), __uint_as_float(w[0] & 0xFFFF0000u), __uint_as_float(w[1] << 16),
+                 __uint_as_float(w[1] & 0xFFFF0000u)};
+    } else {
+      bv = *(const f32x4*)(bias + n);
+    }
+    const f32x4 x = *(const f32x4*)(resid + e) + *(const f32x4*)(gate + (long)b * gate_stride + n) * (y + bv);
+    s4[i] = *(const f32x4*)(seg.shift + (long)b * seg.mod_stride + n);
+    c4[i] = *(const f32x4*)(seg.scale + (long)b * seg.mod_stride + n);
+    v[i] = c < nq ? x : zero;
+    if (c < nq) *(f32x4*)(resid + e) = x;
+    sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+  }
+  const float mean = block_sum(sum, slots[0]) / (float)D;
+  float sq = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const f32x4 d = v[i] - mean;
+    sq += tid + 256 * i < nq ? (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]) : 0.f;
+  }
+  const float rstd = 1.0f / sqrtf(block_sum(sq, slots[1]) / (float)D + eps);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = tid + 256 * i;
+    if (c >= nq) continue;
+    const f32x4 y = (v[i] - mean) * rstd * (1.f + c4[i]) + s4[i];
+    if constexpr (sizeof(WT) == 2)
+      ((u32x2*)seg.out)[(long)row * nq + c] = u32x2{pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    else
+      ((f32x4*)seg.out)[(long)row * nq + c] = y;
+  }
+}
+
+template <typename WT>
+static hipError_t resid_ln_dispatch(const float* part, int S, int M, int N, const WT* bias, const float* gate,
+                                    int gate_stride, float* resid, const LnArgs& ln, hipStream_t st) {
+  const long MN = (long)M * N;
+  if (M == 0) return hipSuccess;
+  const int nv = (N / 4 + 255) / 256;  // hidden <= 4096
+  with_max_parts(S, [&](auto ms) {
+    constexpr int MS = decltype(ms)::value;
+    if (nv <= 1)
+      hipLaunchKernelGGL((splitk_resid_ln_kernel<WT, 1, MS>), dim3(M), dim3(256), 0, st, part, S, MN, N, bias, gate,
+                         gate_stride, resid, ln.s[0], ln.eps);
+    else if (nv <= 2)
+      hipLaunchKernelGGL((splitk_resid_ln_kernel<WT, 2, MS>), dim3(M), dim3(256), 0, st, part, S, MN, N, bias, gate,
+                         gate_stride, resid, ln.s[0], ln.eps);
+    else
+      hipLaunchKernelGGL((splitk_resid_ln_kernel<WT, 4, MS>), dim3(M), dim3(256), 0, st, part, S, MN, N, bias, gate,
+                         gate_stride, resid, ln.s[0], ln.eps);
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_splitk_resid_ln(const float* part, int S, int M, int N, const void* bias, const float* gate,
+                                  int gate_stride, float* resid, const LnArgs& ln, int dtype, hipStream_t st) {
+  return dtype == 1 ? resid_ln_dispatch(part, S, M, N, (const bf16_t*)bias, gate, gate_stride, resid, ln, st)
+                    : resid_ln_dispatch(part, S, M, N, (const float*)bias, gate, gate_stride, resid, ln, st);
+}
+
 // ---------------------------------------------------------------- adaLN GEMV
 // out^T [N, B] = W [N, K] * SiLU(c)^T [K, B] on 16-row MFMA tiles
 // (v_mfma_f32_16x16x32_bf16; for fp32 weights four v_mfma_f32_16x16x4_f32,

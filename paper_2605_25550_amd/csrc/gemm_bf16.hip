@@ -731,18 +731,12 @@ __global__ __launch_bounds__(384 * KG) void gemm_bf16_144_kernel(GemmArgs args) 
 // Split-K reduction: four consecutive outputs per lane, 16-byte loads of
 // each k-range's partial; bias, GELU and bf16 rounding as in the GEMM
 // epilogue.
+template <int MS>
 __global__ __launch_bounds__(256) void splitk_gelu_kernel(const float* __restrict__ part, int S, long MN, int N,
                                                           const bf16_t* __restrict__ bias, bf16_t* __restrict__ out) {
   const long e = (blockIdx.x * 256L + threadIdx.x) * 4;
   if (e >= MN) return;
-  f32x4 y = *(const f32x4*)(part + e);
-  for (int s = 1; s < S; ++s) {
-    const f32x4 p = *(const f32x4*)(part + s * MN + e);
-    y[0] += p[0];
-    y[1] += p[1];
-    y[2] += p[2];
-    y[3] += p[3];
-  }
+  const f32x4 y = sum_parts<MS>(part + e, S, MN);
   const int n = (int)(e % N);
   const u32x2 w = *(const u32x2*)(bias + n);
   const float y0 = y[0] + __uint_as_float(w[0] << 16), y1 = y[1] + __uint_as_float(w[0] & 0xFFFF0000u);
@@ -755,29 +749,24 @@ hipError_t launch_splitk_gelu_bf16(const float* part, int S, int M, int N, const
   const long MN = (long)M * N;
   if (MN == 0) return hipSuccess;
   const long groups = MN / 4;
-  hipLaunchKernelGGL(splitk_gelu_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, part, S, MN, N,
-                     (const bf16_t*)bias, (bf16_t*)out);
+  with_max_parts(S, [&](auto ms) {
+    hipLaunchKernelGGL((splitk_gelu_kernel<decltype(ms)::value>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0,
+                       st, part, S, MN, N, (const bf16_t*)bias, (bf16_t*)out);
+  });
   return hipGetLastError();
 }
 
 // Split-K reduction into the fp32 residual: four consecutive outputs per
 // lane; the ranges are added in order, then the bias, then the gated update
 // as in the GEMM's residual epilogue.
-template <typename BT>
+template <typename BT, int MS>
 __global__ __launch_bounds__(256) void splitk_resid_kernel(const float* __restrict__ part, int S, long MN, int N,
                                                            const BT* __restrict__ bias,
                                                            const float* __restrict__ gate, int gate_stride,
                                                            int rows_per_batch, float* __restrict__ resid) {
   const long e = (blockIdx.x * 256L + threadIdx.x) * 4;
   if (e >= MN) return;
-  f32x4 y = *(const f32x4*)(part + e);
-  for (int s = 1; s < S; ++s) {
-    const f32x4 p = *(const f32x4*)(part + s * MN + e);
-    y[0] += p[0];
-    y[1] += p[1];
-    y[2] += p[2];
-    y[3] += p[3];
-  }
+  const f32x4 y = sum_parts<MS>(part + e, S, MN);
   const long m = e / N;
   const int n = (int)(e - m * N), b = (int)(m / rows_per_batch);
   f32x4 bv;
@@ -802,12 +791,15 @@ hipError_t launch_splitk_resid(const float* part, int S, int M, int N, const voi
   const long MN = (long)M * N;
   if (MN == 0) return hipSuccess;
   dim3 grid((unsigned)((MN / 4 + 255) / 256)), block(256);
-  if (dtype == 1)
-    hipLaunchKernelGGL((splitk_resid_kernel<bf16_t>), grid, block, 0, st, part, S, MN, N, (const bf16_t*)bias, gate,
-                       gate_stride, rows_per_batch, resid);
-  else
-    hipLaunchKernelGGL((splitk_resid_kernel<float>), grid, block, 0, st, part, S, MN, N, (const float*)bias, gate,
-                       gate_stride, rows_per_batch, resid);
+  with_max_parts(S, [&](auto ms) {
+    constexpr int MS = decltype(ms)::value;
+    if (dtype == 1)
+      hipLaunchKernelGGL((splitk_resid_kernel<bf16_t, MS>), grid, block, 0, st, part, S, MN, N, (const bf16_t*)bias,
+                         gate, gate_stride, rows_per_batch, resid);
+    else
+      hipLaunchKernelGGL((splitk_resid_kernel<float, MS>), grid, block, 0, st, part, S, MN, N, (const float*)bias,
+                         gate, gate_stride, rows_per_batch, resid);
+  });
   return hipGetLastError();
 }
 

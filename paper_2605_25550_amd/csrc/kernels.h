@@ -132,6 +132,11 @@ hipError_t launch_splitk_gelu_bf16(const float* part, int S, int M, int N, const
 // b = m / rows_per_batch, ranges added in order s = 0, 1, ...; dtype: of the bias.
 hipError_t launch_splitk_resid(const float* part, int S, int M, int N, const void* bias, const float* gate,
                                int gate_stride, int rows_per_batch, float* resid, int dtype, hipStream_t st);
+// ... and, on the updated rows, the LayerNorm-modulate that follows:
+// ln.s[0].out = LN(resid) * (1 + scale) + shift (one segment whose x is resid,
+// rows_per_batch the same).
+hipError_t launch_splitk_resid_ln(const float* part, int S, int M, int N, const void* bias, const float* gate,
+                                  int gate_stride, float* resid, const LnArgs& ln, int dtype, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmArgs& a, int epi, int tile_cfg, hipStream_t st);
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t st);
 hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, hipStream_t st);

@@ -103,3 +103,35 @@ def test_cond_embed_edges(dtype, hidden, dh, batch):
     ref = O.class_conditioning(t.astype(np.float64), y, **f64({k: sw[k] for k in w}))
     # fp32 arithmetic for both weight types: two chained sums of up to 4096 products
     check("cond", g.host(out), ref, None, 4e-6)
+
+
+# Steps whose residual GEMMs are split: their reductions do the LayerNorms in
+# between, the next block's and the final one (hidden 192: one 4-column group
+# per thread, 1152: two, 2304: three of four); a sequence of blocks against the
+# same blocks called one by one, each of which ends without a LayerNorm.
+@pytest.mark.parametrize("dtype,hidden,dh,batch,t", [("bf16", 192, 64, 1, 40), ("bf16", 1152, 72, 1, 200),
+                                                     ("bf16", 1152, 72, 2, 77), ("bf16", 2304, 72, 1, 65),
+                                                     ("f32", 1152, 72, 2, 333)])
+def test_step_with_split_residuals(dtype, hidden, dh, batch, t):
+    g = _gpu()
+    cfg = _cfg(dtype, hidden, dh, batch=batch, tokens=t, mlp_hidden=4 * hidden).with_(n_blocks=2, grid=None)
+    sw, blocks, inp = synth.step_weights(cfg), [synth.block_weights(cfg, l) for l in range(2)], synth.inputs(cfg)
+    out, _ = g.DeviceStep(cfg, blocks, sw).run(inp["patches"], inp["cond"])
+    from tests.test_parity_gpu import step_ref
+    ref, _ = step_ref(cfg, sw, blocks, inp, None, inp["cond"])
+    check("step", out, ref, None, TOL[dtype])
+
+
+# bf16 attention by grid and length: keys split over the waves (waves without
+# keys, partial query blocks and key tiles, the mask inside a 16-key group,
+# several tiles per wave), the four-wave kernel just past that grid, and the
+# pipelined one from 64 items on.
+ATT = [(64, 64, 1, 1, 0), (256, 128, 1, 31, 0), (576, 72, 1, 65, 0), (576, 72, 1, 129, 0), (576, 72, 2, 203, 6),
+       (256, 64, 1, 257, 0), (256, 128, 1, 641, 0), (576, 72, 1, 1030, 0), (192, 64, 1, 2049, 0),
+       (1024, 128, 5, 200, 0), (1024, 64, 9, 70, 0), (1152, 72, 3, 300, 0), (1024, 64, 4, 385, 0),
+       (1024, 128, 4, 390, 25), (1152, 72, 5, 400, 0)]
+
+
+@pytest.mark.parametrize("hidden,dh,batch,t,tt", ATT)
+def test_attention_dispatch_edges(hidden, dh, batch, t, tt):
+    block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt))
