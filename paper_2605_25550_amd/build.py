@@ -16,7 +16,7 @@ LIB = os.path.join(PKG, "libditmi.so")
 OBJDIR = os.path.join(PKG, "_build")
 ARCH = "gfx950"
 
-SOURCES = ["gemm_bf16.hip", "gemm_f32.hip", "attention_bf16.hip", "attention_f32.hip", "elementwise.hip", "ditmi.cpp"]
+SOURCES = ["gemm_bf16.hip", "gemm_bf16_kg.hip", "gemm_f32.hip", "attention_bf16.hip", "attention_f32.hip", "elementwise.hip", "ditmi.cpp"]
 PROBE = os.path.join(PKG, "gemm_probe")
 
 # Packed-fp32 instructions are disabled for every device compile.

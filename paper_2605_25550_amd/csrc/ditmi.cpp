@@ -87,10 +87,11 @@ struct Layout {
   int ns, Tj, Tj_pad;
 };
 
-int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split);
+int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids = true);
 
 // Bytes of fp32 partials the split GEMMs of this shape need (the largest of
-// the output projection, fc1 and fc2; 0 if none is split).
+// the output projection, fc1 and fc2; 0 if none is split).  The small-grid
+// tiles choose their ranges within what the larger tiles' rules need.
 static size_t split_part_bytes(const dit_shape* s) {
   if (s->dtype != DIT_BF16) return 0;
   const int ns = s->text_tokens > 0 ? 2 : 1;
@@ -106,7 +107,7 @@ static size_t split_part_bytes(const dit_shape* s) {
       p[i].hidden = D;
     }
     int S = 0;
-    choose_tile(p, ns, g[0], SIZE_MAX, &S);
+    choose_tile(p, ns, g[0], SIZE_MAX, &S, false);
     const size_t b = (size_t)S * p[ns - 1].M * p[ns - 1].N * 4;
     if (b > need) need = b;
   }
@@ -290,7 +291,46 @@ static int fill_split(const GemmProb& p, int epi, int bm, int bn, long slots, si
   return 0;
 }
 
-int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split) {
+// Small grids: a call that fits one round of at most 256 workgroups is bound
+// by a workgroup's chain of slice loads, the same rate for every tile
+// measured (K 384..4608, 64..512 rows): 4.2 us + 11.5 us per MB of operand rows
+// a workgroup reads, (BM + BN) K / S 2 bytes.  Among 64 x 32, 64 x 64, 64 x 96
+// (gemm_bf16_kg.hip) and 64 x 128 in S k-ranges, the least of that plus, with
+// S > 1, 3 us and the partial traffic at 5 TB/s for the reduction (which may
+// take the next LayerNorm along).  E.g. the output projection at 256 rows of
+// DiT-XL/2: 64 x 32 whole, 144 workgroups, 6.2 us against 6.4 + 3.6 for 64 x 128
+// in three ranges; fc2: 64 x 64 in three ranges 9.4 us, 64 x 128 in six 9.5.
+// 288 tiles, just over a round, are slower than 64 x 128 in every case (fc1 at
+// 512 rows 14.7 us against 15.1-17.6), so beyond a round the rules below hold.
+// Returns the tile or -1.
+static int small_grid(const GemmProb* p, int np, int epi, size_t part_cap, int* split) {
+  static const int cfgs[] = {TILE_64x128, TILE_64x96, TILE_64x64, TILE_64x32};
+  const bool can_split = np == 1 && (epi == EPI_GELU || epi == EPI_RESID || epi == EPI_RESID2);
+  int best = -1;
+  double best_us = 0.0;
+  for (int cfg : cfgs) {
+    int bm = 0, bn = 0;
+    gemm_tile_dims(cfg, &bm, &bn);
+    long tiles = 0;
+    bool ok = true;
+    for (int i = 0; i < np; ++i) {
+      tiles += (long)((p[i].M + bm - 1) / bm) * ((p[i].N + bn - 1) / bn);
+      ok = ok && (epi != EPI_QKV || (2 * p[i].hidden) % bn == 0);  // tiles may not straddle k | v
+    }
+    if (!ok) continue;
+    const int ks = p[0].K / 64;
+    for (int S = 1; S <= (can_split ? 8 : 1); ++S) {
+      if (tiles * S > 256) break;
+      const double mn = (double)p[0].M * p[0].N;
+      if (S > 1 && (ks / S < 4 || ks % S != 0 || S * mn * 4 > (double)part_cap)) continue;
+      const double us = 4.2 + 11.5e-6 * (bm + bn) * 2.0 * p[0].K / S + (S > 1 ? 3.0 + (S * 4.0 + 8.0) * mn / 5e6 : 0.0);
+      if (best < 0 || us < best_us) best = cfg, best_us = us, *split = S > 1 ? S : 0;
+    }
+  }
+  return best;
+}
+
+int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids) {
   *split = 0;
   long t128 = 0, t144 = 0, t256 = 0, t2x1 = 0, t192 = 0;
   bool n144 = true, ok256 = true, ok128 = true, ok192 = epi != EPI_RESID && epi != EPI_RESID2;
@@ -325,6 +365,10 @@ int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split)
       *split = best_split;
       return best;
     }
+  }
+  if (small_grids) {
+    const int cfg = small_grid(p, np, epi, part_cap, split);
+    if (cfg >= 0) return cfg;
   }
   const int cfg = ((t128 >= 256 && t128 < 512) || t128 >= 768) ? TILE_128x128
                   : t128 >= 512                                   ? TILE_64x128_S2

@@ -811,6 +811,9 @@ void gemm_tile_dims(int tile_cfg, int* bm, int* bn) {
     case TILE_256x256: *bm = 256; *bn = 256; break;
     case TILE_256x128: *bm = 256; *bn = 128; break;
     case TILE_256x192: *bm = 256; *bn = 192; break;
+    case TILE_64x32: *bm = 64; *bn = 32; break;
+    case TILE_64x64: *bm = 64; *bn = 64; break;
+    case TILE_64x96: *bm = 64; *bn = 96; break;
     default: *bm = 64; *bn = 128; break;
   }
 }
@@ -865,6 +868,9 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tile_cfg, hipStream_
     case TILE_256x256: return launch_tile<256, 256, 2, 4, 2>(a, epi, st);
     case TILE_256x128: return launch_tile<256, 128, 4, 2, 3>(a, epi, st);
     case TILE_256x192: return launch_tile<256, 192, 4, 2, 2>(a, epi, st);
+    case TILE_64x32:
+    case TILE_64x64:
+    case TILE_64x96: return launch_gemm_bf16_kg(a, epi, tile_cfg, st);
     default: return launch_tile<128, 128, 2, 2, 2>(a, epi, st);
   }
 }

@@ -124,6 +124,7 @@ struct AdaArgs {
 // ------------------------------------------------------------------ launchers
 // Each returns hipSuccess or the launch error.  dtype: 0 = fp32, 1 = bf16.
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tile_cfg, hipStream_t st);
+hipError_t launch_gemm_bf16_kg(const GemmArgs& a, int epi, int tile_cfg, hipStream_t st);  // its TILE_64x{32,64,96}
 // out[m][n] = bf16(GELU(sum_{s < S} part[s][m][n] + bias[n])), ranges added in
 // order s = 0, 1, ...; M * N elements, N a multiple of 4.
 hipError_t launch_splitk_gelu_bf16(const float* part, int S, int M, int N, const void* bias, void* out,
@@ -162,7 +163,8 @@ enum {
   TILE_128x128 = 0, TILE_64x128 = 1, TILE_64x128_S2 = 2, TILE_64x144 = 3,
   TILE_256x256 = 4, TILE_256x128 = 5, TILE_256x192 = 6,
   TILE_64x144_1 = 7,  // 64 x 144 with one k-group of six waves (two workgroups per CU)
-  TILE_COUNT = 8
+  TILE_64x32 = 8, TILE_64x64 = 9, TILE_64x96 = 10,  // gemm_bf16_kg.hip
+  TILE_COUNT = 11
 };
 void gemm_tile_dims(int tile_cfg, int* bm, int* bn);
 // ... and of the fp32 GEMM.

@@ -105,6 +105,21 @@ def test_cond_embed_edges(dtype, hidden, dh, batch):
     check("cond", g.host(out), ref, None, 4e-6)
 
 
+# Small grids (one round of 64 x 32, 64 x 64, 64 x 96 or 64 x 128 tiles, k-ranges
+# with the residual reduction): hidden 64 (fewer k-slices than k-groups),
+# ragged rows, tiles that straddle samples, q/k padding of head_dim 72, v^T
+# columns of samples that start off a four-key group, joint streams, one
+# 256-row round and the first grid past it.
+SMALL_GRID = [(64, 64, 1, 1, 0), (64, 64, 2, 67, 5), (192, 64, 3, 21, 0), (576, 72, 3, 85, 0), (576, 72, 2, 63, 9),
+              (1152, 72, 1, 64, 0), (1152, 72, 1, 256, 0), (1152, 72, 1, 333, 0), (1152, 72, 2, 257, 0),
+              (1152, 72, 3, 333, 0), (768, 64, 2, 130, 30), (256, 128, 5, 50, 0), (384, 64, 1, 700, 0)]
+
+
+@pytest.mark.parametrize("hidden,dh,batch,t,tt", SMALL_GRID)
+def test_small_grid_edges(hidden, dh, batch, t, tt):
+    block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=4 * hidden))
+
+
 # Steps whose residual GEMMs are split: their reductions do the LayerNorms in
 # between, the next block's and the final one (hidden 192: one 4-column group
 # per thread, 1152: two, 2304: three of four); a sequence of blocks against the
