@@ -654,10 +654,86 @@ __global__ __launch_bounds__(256) void patch_tile_kernel(int rows, int T, int P,
   }
 }
 
+// Channels in whole 16s (patch_mfma_kernel): v_mfma_f32_16x16x4_f32 (exact fp32
+// products, fp32 accumulation from the bias on).  A wave owns 64 columns and
+// PM_ROWS rows: A = the weights (converted to fp32 once per 64 channels, kept
+// in registers for all its rows), B = the latent rows, both 16 bytes of fp32 per
+// lane and 16 channels straight from global memory.  Column n = 16 kq + 4 j + e
+// of the 64 is row 4 kq + e of tile j, so a lane ends with 16 consecutive
+// columns of one row and a row is stored as 256 contiguous bytes.  Bound by
+// the stores (x is 4 D bytes a row).  64 channels, 2000 rows of 1536: 21.4 us (the
+// tile kernel above) -> 16.4; 16 channels, 4096 rows of 3072: 33.7 us (a
+// workgroup per row) -> 26.1, 256 rows of 1152: 6.8 -> 4.9.
+constexpr int PM_ROWS = 32;
+
+template <typename WT>
+__global__ __launch_bounds__(256) void patch_mfma_kernel(int rows, int T, int P, int D, const float* __restrict__ z,
+                                                         const WT* __restrict__ w, const WT* __restrict__ bias,
+                                                         const float* __restrict__ pos, float* __restrict__ x) {
+  constexpr int RT = PM_ROWS / 16;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
+  const int n0 = blockIdx.x * 64, row0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * PM_ROWS;
+  if (row0 >= rows) return;
+  const WT* wr = w + (long)(n0 + 16 * (r16 >> 2) + (r16 & 3)) * P + 4 * kq;  // tile j: + 4 j rows
+  const float* zr[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) zr[t] = z + (long)min(row0 + 16 * t + r16, rows - 1) * P + 4 * kq;
+  f32x4 acc[RT][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    f32x4 b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = ld_as_float<WT>(bias, n0 + 16 * kq + 4 * j + e);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) acc[t][j] = b;
+  }
+  for (int p0 = 0; p0 < P; p0 += 64) {
+    f32x4 wv[4][4], zv[RT][4];  // [16-channel step][column tile], [row tile][step]
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (p0 + 16 * s < P) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wv[s][j] = ld_w4(wr + (long)4 * j * P + p0 + 16 * s);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) zv[t][s] = *(const f32x4*)(zr[t] + p0 + 16 * s);
+      }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      if (p0 + 16 * s < P)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[s][j][e], zv[t][s][e], acc[t][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int row = row0 + 16 * t + r16, n = n0 + 16 * kq;
+    if (row >= rows) continue;
+    const float* pr = pos ? pos + (long)(row % T) * D + n : nullptr;  // 4-byte aligned
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f32x4 v = acc[t][j];
+      if (pos)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += pr[4 * j + e];
+      *(f32x4*)(x + (long)row * D + n + 4 * j) = v;
+    }
+  }
+}
+
 template <typename WT>
 static void launch_patch_embed_t(int rows, int T, int P, int D, const float* z, const WT* w, const WT* b,
                                  const float* pos, float* x, hipStream_t st) {
-  if (P <= 16)
+  // the MFMA kernel's loads are 4 consecutive channels: whole 16s of channels
+  // and latents and weights aligned for it (the entry points ask for 4 bytes only)
+  const bool mfma = P % 16 == 0 && (uintptr_t)z % 16 == 0 && (uintptr_t)w % (4 * sizeof(WT)) == 0;
+  if (mfma)
+    hipLaunchKernelGGL((patch_mfma_kernel<WT>), dim3(D / 64, (rows + 4 * PM_ROWS - 1) / (4 * PM_ROWS)), dim3(256), 0,
+                       st, rows, T, P, D, z, w, b, pos, x);
+  else if (P <= 16)
     hipLaunchKernelGGL((patch_row_kernel<WT>), dim3(rows), dim3(256), 0, st, T, P, D, z, w, b, pos, x);
   else
     hipLaunchKernelGGL((patch_tile_kernel<WT>), dim3((D + 255) / 256, (rows + PT_ROWS - 1) / PT_ROWS), dim3(256), 0,

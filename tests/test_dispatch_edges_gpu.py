@@ -150,3 +150,29 @@ ATT = [(64, 64, 1, 1, 0), (256, 128, 1, 31, 0), (576, 72, 1, 65, 0), (576, 72, 1
 @pytest.mark.parametrize("hidden,dh,batch,t,tt", ATT)
 def test_attention_dispatch_edges(hidden, dh, batch, t, tt):
     block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt))
+
+
+# Patch embedding: channels in whole 16s on the matrix cores (one 16-channel
+# step, a partial and several 64-channel passes, ragged rows, position table or
+# none), other channel counts and misaligned latents on the other kernels.
+@pytest.mark.parametrize("dtype,hidden,dh,batch,grid,p,shift", [
+    ("bf16", 64, 64, 1, (1, 1), 16, 0), ("bf16", 192, 64, 3, (5, 7), 48, 0), ("f32", 128, 64, 2, (9, 15), 80, 0),
+    ("bf16", 128, 128, 1, (8, 17), 256, 0), ("bf16", 192, 64, 2, (5, 9), 64, 1), ("f32", 64, 64, 1, (3, 11), 16, 1),
+    ("bf16", 64, 64, 1, (6, 6), 20, 0), ("bf16", 64, 64, 2, (4, 4), 7, 0), ("bf16", 256, 64, 1, None, 64, 0)])
+def test_patch_embed_edges(dtype, hidden, dh, batch, grid, p, shift):
+    import paper_2605_25550_amd as dm
+    g = _gpu()
+    t = grid[0] * grid[1] if grid else 33
+    cfg = _cfg(dtype, hidden, dh, batch=batch, tokens=t, mlp_hidden=64).with_(grid=grid, patch_in=p, patch_out=4)
+    sw, blocks, inp = synth.step_weights(cfg), [synth.block_weights(cfg, 0)], synth.inputs(cfg)
+    pos = O.pos_embed_2d(*grid, hidden) if grid else None
+    ds = g.DeviceStep(cfg, blocks, sw)
+    buf = torch.zeros(batch * t * p + 1, device="cuda")  # latents need only 4-byte alignment
+    z = buf[shift:shift + batch * t * p].view(batch, t, p)
+    z.copy_(g.dev(inp["patches"]))
+    out = torch.empty((batch, t, 4), device="cuda")
+    dm.step_forward(ds.shape, ds.table, z, g.dev(inp["cond"]), out, ds.ws)
+    torch.cuda.synchronize()
+    from tests.test_parity_gpu import step_ref
+    ref, _ = step_ref(cfg, sw, blocks, inp, pos, inp["cond"])
+    check("step", g.host(out), ref, None, TOL[dtype])
