@@ -87,6 +87,7 @@ struct Layout {
   int ns, Tj, Tj_pad;
 };
 
+// *split: k-ranges of the last problem (0: none), negative: of both problems.
 int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids = true);
 
 // Bytes of fp32 partials the split GEMMs of this shape need (the largest of
@@ -330,6 +331,32 @@ static int small_grid(const GemmProb* p, int np, int epi, size_t part_cap, int* 
   return best;
 }
 
+// Whole split: residual GEMMs (one problem or both streams) with too few
+// 256 x 128 tiles for a round but a long K run those tiles in S k-ranges, all
+// problems, instead of 64-row tiles over the whole of K.  Measured per launch
+// at K = 96 slices, 2154 x 1536: 45 + 9 us (two ranges and their reduction)
+// against 62-81 for 64 x 128; at 24 slices 19 + 9 against 21, not worth it.
+// Estimates: 8.5 us + 0.76 us per slice of a unit and 2 us per reduction + its
+// traffic at 7 TB/s, against 5.8 us + 0.66 us per slice for up to 512 tiles of
+// 64 x 128 (two per CU).  Returns S, or 0.
+static int whole_split(const GemmProb* p, int np, int epi, size_t part_cap) {
+  if (epi != EPI_RESID && epi != EPI_RESID2) return 0;
+  long t = 0, t64 = 0;
+  double mn = 0;
+  for (int i = 0; i < np; ++i) {
+    t += (long)((p[i].M + 255) / 256) * ((p[i].N + 127) / 128);
+    t64 += (long)((p[i].M + 63) / 64) * ((p[i].N + 127) / 128);
+    mn += (double)p[i].M * p[i].N;
+  }
+  const int ks = p[0].K / 64;
+  const double whole = (double)((t64 + 511) / 512) * (5.8 + 0.66 * ks);
+  for (int S = 4; S >= 2; --S) {
+    if (t * S > 256 || 2 * t * S <= 256 || ks % S != 0 || S * mn * 4 > (double)part_cap) continue;
+    if (8.5 + 0.76 * ks / S + 2.0 * np + (S * 4.0 + 8.0) * mn / 7e6 < 0.9 * whole) return S;
+  }
+  return 0;
+}
+
 int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids) {
   *split = 0;
   long t128 = 0, t144 = 0, t256 = 0, t2x1 = 0, t192 = 0;
@@ -369,6 +396,11 @@ int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split,
   if (small_grids) {
     const int cfg = small_grid(p, np, epi, part_cap, split);
     if (cfg >= 0) return cfg;
+    const int S = whole_split(p, np, epi, part_cap);
+    if (S) {
+      *split = np == 2 ? -S : S;  // negative: both problems
+      return TILE_256x128;
+    }
   }
   const int cfg = ((t128 >= 256 && t128 < 512) || t128 >= 768) ? TILE_128x128
                   : t128 >= 512                                   ? TILE_64x128_S2
@@ -496,7 +528,13 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
     tcfg = f32_plan(a.p, a.nprob, G.epi, G.part_cap, &split);
     gemm_f32_tile_dims(tcfg, &bm, &bn);
   }
+  // Split problems: the second of two (tail schedule), the only one (fill
+  // split, every unit in one round, the usual tile order) or both.
+  const bool both = split < 0;
+  if (both) split = -split;
+  const int sp = both ? 0 : a.nprob - 1;  // the first split problem
   int tiles = 0;
+  size_t part_at = 0;
   for (int i = 0; i < a.nprob; ++i) {
     GemmProb& p = a.p[i];
     p.tiles_m = (p.M + bm - 1) / bm;
@@ -504,41 +542,40 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
     const double esz = dtype == DIT_BF16 ? 2.0 : 4.0;
     p.group_m = group_height(p.tiles_m, p.tiles_n, bm, bn, dtype == DIT_BF16 ? tcfg : -1, esz * p.M * p.K,
                              esz * p.N * p.K);
+    const bool parts = split && i >= sp;
     p.tile_begin = tiles;
-    p.ksplit = 0;
-    p.part = nullptr;
-    tiles += p.tiles_m * p.tiles_n * (i == 1 && split ? split : 1);
+    p.ksplit = parts ? split : 0;
+    p.part = parts ? G.part + part_at : nullptr;
+    if (parts) part_at += (size_t)split * p.M * p.N;
+    tiles += p.tiles_m * p.tiles_n * (parts ? split : 1);
   }
-  // The split problem is the second of two (tail schedule) or the only one
-  // (fill split, every unit in one round, the usual tile order).
-  const int sp = a.nprob - 1;
-  if (split && sp == 0) tiles *= split;
   a.total_tiles = tiles;
   a.tail = split && sp == 1 ? 1 : 0;
-  if (split) {  // fp32: always the only problem
-    a.p[sp].ksplit = split;
-    a.p[sp].part = G.part;
-  }
   if (tiles == 0) return hipSuccess;
   hipError_t e = timed(G.kclass, G.flops, G.bytes, st, [&]() {
     return dtype == DIT_BF16 ? launch_gemm_bf16(a, G.epi, tcfg, st) : launch_gemm_f32(a, G.epi, tcfg, st);
   });
-  if (e != hipSuccess || !split) return e;
-  const GemmProb& q = a.p[sp];
-  const double mn = (double)q.M * q.N;
-  if (G.epi == EPI_GELU)
-    return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 2.0) + q.N * 2.0, st, [&]() {
-      return launch_splitk_gelu_bf16(q.part, split, q.M, q.N, q.bias, q.out, st);
-    });
-  if (G.ln && G.ln->nseg == 1 && a.nprob == 1) {
-    G.ln_done = true;
-    return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0 + (dtype == DIT_BF16 ? 2.0 : 4.0)), st, [&]() {
-      return launch_splitk_resid_ln(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.resid, *G.ln, dtype, st);
-    });
+  for (int i = sp; i < a.nprob && split && e == hipSuccess; ++i) {
+    const GemmProb& q = a.p[i];
+    const double mn = (double)q.M * q.N;
+    if (G.epi == EPI_GELU) {
+      e = timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 2.0) + q.N * 2.0, st, [&]() {
+        return launch_splitk_gelu_bf16(q.part, split, q.M, q.N, q.bias, q.out, st);
+      });
+    } else if (G.ln && G.ln->nseg == 1 && a.nprob == 1) {
+      G.ln_done = true;
+      e = timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0 + (dtype == DIT_BF16 ? 2.0 : 4.0)), st, [&]() {
+        return launch_splitk_resid_ln(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.resid, *G.ln, dtype,
+                                      st);
+      });
+    } else {
+      e = timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0) + q.N * 2.0, st, [&]() {
+        return launch_splitk_resid(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.rows_per_batch, q.resid,
+                                   dtype, st);
+      });
+    }
   }
-  return timed(DIT_K_OTHER, 0, mn * (split * 4.0 + 8.0) + q.N * 2.0, st, [&]() {
-    return launch_splitk_resid(q.part, split, q.M, q.N, q.bias, q.gate, q.gate_stride, q.rows_per_batch, q.resid, dtype, st);
-  });
+  return e;
 }
 
 // ------------------------------------------------------------------ block sequence
@@ -731,8 +768,10 @@ dit_status run_block(const dit_shape* s, const Layout& L, char* ws, StreamIO* io
       p.gate = io[i].mod + 5 * D;
       p.gate_stride = 6 * D;
     }
-    G.part = (float*)(ws + L.part);
-    G.part_cap = L.part_cap;
+    // o is dead by now too: q, k, v and o are one span
+    const size_t span = L.g - L.q;
+    G.part = (float*)(ws + (span > L.part_cap ? L.q : L.part));
+    G.part_cap = std::max(span, L.part_cap);
     G.flops = 2.0 * tokens * D * F;
     G.bytes = (tokens * F + ns * (double)D * F) * E + tokens * D * 8.0;
     HIP_TRY(run_gemm(G, dt, st));

@@ -176,3 +176,11 @@ def test_patch_embed_edges(dtype, hidden, dh, batch, grid, p, shift):
     from tests.test_parity_gpu import step_ref
     ref, _ = step_ref(cfg, sw, blocks, inp, pos, inp["cond"])
     check("step", g.host(out), ref, None, TOL[dtype])
+
+
+# Residual GEMMs whose k-ranges cover both streams: fc2 of the joint block at
+# 1900 + 140 rows (64 256 x 128 tiles would be a quarter round), and one stream.
+@pytest.mark.parametrize("hidden,dh,f,batch,t,tt", [(1024, 64, 6144, 2, 1900, 70), (1536, 64, 6144, 2, 1000, 77),
+                                                    (1536, 128, 6144, 1, 2100, 0)])
+def test_whole_split_edges(hidden, dh, f, batch, t, tt):
+    block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=f))
