@@ -849,14 +849,17 @@ __global__ __launch_bounds__(256) void attn_bf16_split_kernel(AttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) m = fmaxf(m, s[kt][e]);
     const float m_new = fmaxf(m_run, max_halves(m));
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    // where every score so far overflowed to -inf the wave adds nothing (other
+    // waves may hold finite ones): exp2(-inf - 0) instead of -inf - (-inf)
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
     m_run = m_new;
     float lsum = 0.f;
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        s[kt][e] = __builtin_amdgcn_exp2f(s[kt][e] - m_new);
+        s[kt][e] = __builtin_amdgcn_exp2f(s[kt][e] - m_ref);
         lsum += s[kt][e];
       }
     l_run = l_run * alpha + lsum;

@@ -126,7 +126,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
       mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
       const float m_new = fmaxf(m_run[t], mt);
-      const float alpha = expf(m_run[t] - m_new);
+      // where every score so far overflowed to -inf the wave adds nothing (other
+      // waves may hold finite ones): exp(-inf - 0) instead of -inf - (-inf)
+      const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m_run[t] - m_ref);
       m_run[t] = m_new;
       l_run[t] *= alpha;
 #pragma unroll
@@ -135,7 +138,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
       for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          s[t][c][e] = expf(s[t][c][e] - m_new);
+          s[t][c][e] = expf(s[t][c][e] - m_ref);
           l_run[t] += s[t][c][e];
         }
     }

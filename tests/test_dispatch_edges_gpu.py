@@ -184,3 +184,27 @@ def test_patch_embed_edges(dtype, hidden, dh, batch, grid, p, shift):
                                                     (1536, 128, 6144, 1, 2100, 0)])
 def test_whole_split_edges(hidden, dh, f, batch, t, tt):
     block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=f))
+
+
+# Keys split over the waves: a wave whose only key scores -inf against every
+# query (the product overflows fp32) adds nothing to the others' results.
+# Tokens are Walsh patterns, which LayerNorm keeps (mean 0, variance 1): the
+# last one meets the only non-zero row of W_k, the others are orthogonal to it.
+@pytest.mark.parametrize("dtype,t", [("bf16", 65), ("f32", 33)])
+def test_attention_wave_of_overflowed_scores(dtype, t):
+    cfg = _cfg(dtype, 64, 64, batch=1, tokens=t).with_(ln_eps=1e-20)  # 1 + eps is 1 in 64 bits: exact patterns
+    walsh = np.array([[(-1.0) ** bin(i & j).count("1") for i in range(64)] for j in range(64)], dtype=np.float32)
+    w, inp = synth.block_weights(cfg, 0), synth.inputs(cfg)
+    img = w["img"]
+    img["w_ada"][:] = 0
+    img["b_ada"][:] = 0
+    img["b_ada"][2 * 64:3 * 64] = 1  # attention gate; the MLP's stays 0
+    img["w_qkv"][:128] = 0
+    img["b_qkv"][:128] = 0
+    img["b_qkv"][0] = 2.0 ** 66
+    img["w_qkv"][64] = walsh[1] * 2.0 ** 63
+    x = walsh[2 + np.arange(t) % 62][None].copy()
+    x[0, -1] = -walsh[1]
+    y, _ = _gpu().run_block(cfg, w, x, inp["cond"], None)
+    ref = O.dit_block(x, inp["cond"], f64(img), cfg.heads, cfg.ln_eps)
+    check("img", y, ref, x, TOL[dtype])
