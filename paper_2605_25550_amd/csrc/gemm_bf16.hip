@@ -860,6 +860,10 @@ static hipError_t launch_tile(const GemmArgs& a, int epi, hipStream_t st) {
 // workgroup per CU.  256x256 (2 slots, 128 KB) and 256x128 (3 slots, 144 KB)
 // run one eight-wave workgroup per CU.
 hipError_t launch_gemm_bf16(const GemmArgs& a, int epi, int tile_cfg, hipStream_t st) {
+  // the 64 x 144 kernel has no k-ranges: a grid of them would index past its tiles
+  if (tile_cfg == TILE_64x144 || tile_cfg == TILE_64x144_1)
+    for (int i = 0; i < a.nprob; ++i)
+      if (a.p[i].ksplit > 1) return hipErrorInvalidValue;
   switch (tile_cfg) {
     case TILE_64x128: return launch_tile<64, 128, 2, 2, 3>(a, epi, st);
     case TILE_64x128_S2: return launch_tile<64, 128, 2, 2, 2>(a, epi, st);
