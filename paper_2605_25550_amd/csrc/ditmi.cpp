@@ -267,14 +267,14 @@ static int tail_split(const GemmProb* p, int np, int epi, int bm, int bn, size_t
 // of a round.
 static double tail_rounds(long t0, int S) { return (double)(t0 / 256) + 1.0 / S + 0.15; }
 
-// Fill split: a single problem whose tiles cannot fill the GPU is split
-// into S equal k-ranges of at least 4 slices, e.g. the DiT-XL/2 fc2 at one
-// sample of 256 tokens: 36 tiles of 64 x 128, each 72 k-slices long, as 216
-// units of 12 slices.  Up to 128 tiles the units are at most one per CU
-// (256; measured faster than more, smaller units sharing CUs); up to half
-// of `slots` (the workgroups resident at once: 256 CUs x workgroups per CU)
-// they may fill the slots.  S is the largest such split for which the
-// estimated gain
+// Fill split, which sizes the partials of small grids in the workspace
+// (split_part_bytes); the ranges are chosen within that size by small_grid and
+// whole_split.  A single problem whose tiles cannot fill the GPU in S equal
+// k-ranges of at least 4 slices, e.g. the DiT-XL/2 fc2 at one sample of 256
+// tokens: 36 tiles of 64 x 128, each 72 k-slices long, as 216 units of 12.  Up
+// to 128 tiles the units are at most one per CU, up to half of `slots` (the
+// workgroups resident at once) they may fill the slots.  S is the largest
+// such split for which the estimated gain
 //   (1 - 1/S) * 0.45 us per slice - partial traffic at 5 TB/s - 3 us
 // of reduction launch is positive.  Returns S (0: no split).
 static int fill_split(const GemmProb& p, int epi, int bm, int bn, long slots, size_t part_cap) {
@@ -405,7 +405,9 @@ int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split,
   const int cfg = ((t128 >= 256 && t128 < 512) || t128 >= 768) ? TILE_128x128
                   : t128 >= 512                                   ? TILE_64x128_S2
                                                                   : TILE_64x128;
-  if (np == 1) {
+  // With small_grids, grids that fill_split could split (tiles <= slots / 2)
+  // have been taken by the rules above.
+  if (np == 1 && !small_grids) {
     int bm = 0, bn = 0;
     gemm_tile_dims(cfg, &bm, &bn);
     // resident workgroups per CU (LDS): 128x128 and 64x128 with 3 slots two, 64x128 with 2 slots three
