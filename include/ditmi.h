@@ -41,8 +41,9 @@
  *     calls can be captured into a HIP graph.
  *   - Size limits (DIT_ERR_UNSUPPORTED beyond them): rows = B * (T + Tt)
  *     below 2^24 with rows * max(3D, F) below 2^31, and every weight matrix
- *     (in particular F * D) below 2^31 elements, so that all byte offsets
- *     inside one operand fit the kernels' 32-bit address arithmetic.
+ *     (in particular F * D) below 2^31 elements: element indices fit 32 bits,
+ *     and so do the byte offsets of bf16 operands (fp32 operands, up to 8 GiB,
+ *     are addressed with 64 bits).
  */
 #ifndef DITMI_H
 #define DITMI_H

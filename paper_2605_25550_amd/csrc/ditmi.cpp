@@ -62,10 +62,10 @@ dit_status check_shape(const dit_shape* s, bool step) {
   const long widest = s->mlp_hidden > 3 * s->hidden ? s->mlp_hidden : 3L * s->hidden;
   if (rows * widest >= (1L << 31) || rows >= (1L << 24))
     return fail(DIT_ERR_UNSUPPORTED, "batch*tokens (%ld rows) too large", rows);
-  // The GEMM's DMA lane offsets (row * K * 2 bytes) and the adaLN/GEMV row
-  // offsets are 32-bit: every weight matrix stays below 2^31 elements.  The
-  // largest are fc1 / fc2 with F * D elements (w_ada 6 D^2 and w_qkv 3 D^2
-  // are bounded by hidden <= 4096).
+  // The bf16 GEMM's DMA lane offsets (row * K * 2 bytes) are 32-bit: operands
+  // stay below 2^31 elements, i.e. 4 GiB.  The same limits in fp32 are 8 GiB, so
+  // the fp32 GEMM has 64-bit tile bases.  The largest weights are fc1 / fc2 with
+  // F * D elements (w_ada 6 D^2 and w_qkv 3 D^2 are bounded by hidden <= 4096).
   if ((long)s->mlp_hidden * s->hidden >= (1L << 31))
     return fail(DIT_ERR_UNSUPPORTED, "mlp_hidden * hidden (%d * %d) >= 2^31 elements: weight matrix too large",
                 s->mlp_hidden, s->hidden);
@@ -505,6 +505,7 @@ static int f32_plan(const GemmProb* p, int np, int epi, size_t part_cap, int* sp
   double best_us = -1.0;
   *split = 0;
   for (int cfg = 0; cfg < F32_COUNT; ++cfg) {
+    if (!gemm_f32_tile_fits(cfg, p[0].K)) continue;
     int bm = 0, bn = 0;
     gemm_f32_tile_dims(cfg, &bm, &bn);
     long tiles = 0;

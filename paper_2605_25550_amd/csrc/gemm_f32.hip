@@ -22,6 +22,8 @@
 // 120 -> 53 us, output projection 74 -> 22, fc1 136 -> 63, fc2 274 -> 68 (with
 // its reduction; 104 TFLOP/s); 256 rows at hidden 384: 31, 29, 27, 94 -> 7.4,
 // 5.6, 7.4, 10.9 us; 2048 rows at hidden 1152: fc1 177 us (123 TFLOP/s).
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -84,18 +86,22 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64) void gemm_f32_kernel(GemmArgs 
   const unsigned ring = (unsigned)(kg * ST * C::SLICE);
   const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem)) + ring;
 
-  // DMA instruction t of this wave fills slice rows 8q .. 8q+7, q = wave + NW t
+  // DMA instruction t of this wave fills slice rows 8q .. 8q+7, q = wave + NW t.
+  // Lane offsets are 32 bits and an fp32 operand may hold up to 8 GiB (2^31
+  // elements), so they count from the tile's first row, which is part of the
+  // 64-bit base (gemm_f32_tile_fits: such offsets fit).
+  const long a_tile = (unsigned)m0 * (unsigned)K, w_tile = (unsigned)n0 * (unsigned)K;
   unsigned voff[C::IPW];
 #pragma unroll
   for (int t = 0; t < C::IPW; ++t) {
     const int q = wave + C::NW * t, row = 8 * q + (lane >> 3);
-    const int grow = q < C::BM / 8 ? min(m0 + row, M - 1) : min(n0 + row - C::BM, N - 1);  // clamped: ragged tiles
-    voff[t] = (unsigned)grow * (unsigned)K * 4u + (unsigned)(((lane & 7) ^ (lane >> 3) ^ (q & 1)) * 16);
+    const int trow = q < C::BM / 8 ? min(row, M - 1 - m0) : min(row - C::BM, N - 1 - n0);  // clamped: ragged tiles
+    voff[t] = (unsigned)trow * (unsigned)K * 4u + (unsigned)(((lane & 7) ^ (lane >> 3) ^ (q & 1)) * 16);
   }
   auto issue = [&](int i, int t) __attribute__((always_inline)) {  // instruction t of slice i of this k-group
     const long k0 = (long)(kb + kg + i * KG) * 32;
     const int q = wave + C::NW * t;
-    dma_16s((q < C::BM / 8 ? (const float*)P.A : (const float*)P.W) + k0, voff[t],
+    dma_16s(q < C::BM / 8 ? (const float*)P.A + (a_tile + k0) : (const float*)P.W + (w_tile + k0), voff[t],
             lds0 + (unsigned)((i % ST) * C::SLICE + q * 1024));
   };
 
@@ -232,6 +238,12 @@ void gemm_f32_tile_dims(int tile_cfg, int* bm, int* bn) {
   const int dims[F32_COUNT][2] = {{32, 32}, {64, 64}, {96, 64}, {96, 48}};
   *bm = dims[tile_cfg][0];
   *bn = dims[tile_cfg][1];
+}
+
+bool gemm_f32_tile_fits(int tile_cfg, int K) {
+  int bm = 0, bn = 0;
+  gemm_f32_tile_dims(tile_cfg, &bm, &bn);
+  return (uint64_t)(std::max(bm, bn) - 1) * K * 4 + 128 <= UINT32_MAX;
 }
 
 template <int WGM, int WGN, int KG, int TM, int TN, int ST>

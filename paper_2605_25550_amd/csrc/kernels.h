@@ -170,5 +170,9 @@ void gemm_tile_dims(int tile_cfg, int* bm, int* bn);
 // ... and of the fp32 GEMM.
 enum { F32_32x32 = 0, F32_64x64, F32_96x64, F32_96x48, F32_COUNT };
 void gemm_f32_tile_dims(int tile_cfg, int* bm, int* bn);
+// Whether the fp32 GEMM's 32-bit lane offsets reach the tile's last row: K below
+// 11.3 million for 96 rows, 17 for 64; 32 rows always (mlp_hidden * hidden < 2^31
+// and hidden >= 64 keep K below 2^25).
+bool gemm_f32_tile_fits(int tile_cfg, int K);
 
 }  // namespace ditmi

@@ -77,7 +77,7 @@ def test_workspace_rejects_bad_shapes(dm, field, value, status):
 
 def test_weight_matrix_size_limit(dm):
     """A weight matrix of 2^31 or more elements (F * D) is rejected before any
-    launch: the kernels address one operand with 32-bit byte offsets.  Hidden
+    launch: the bf16 GEMM addresses one operand with 32-bit byte offsets.  Hidden
     4096 with MLP width 524288 is a 4 GiB fc1 weight, which the HBM could
     hold; one width step below the limit is accepted."""
     s = shape(dm, "c1", batch=1, tokens=16, hidden=4096, heads=32, head_dim=128, mlp_hidden=524288)
