@@ -519,12 +519,16 @@ __global__ __launch_bounds__(NW * 64) void cond_out_kernel(int B, int N, int K, 
       float acc[NS] = {};
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const int k = min((256 * g + lane * 4) * E, K - 4 * E);  // past the end the weights are zero
+        // lanes past the row's end add nothing (zero weights would not do: 0 x inf)
+        const bool in_row = (256 * g + lane * 4) * E < K;
+        const int k = in_row ? (256 * g + lane * 4) * E : K - 4 * E;
 #pragma unroll
-        for (int i = 0; i < NS; ++i)
+        for (int i = 0; i < NS; ++i) {
+          float s = acc[i];
 #pragma unroll
-          for (int e = 0; e < E; ++e)
-            acc[i] = dot4(w[g][e], *(const f32x4*)&in[min(b + i, nb - 1) * K + k + 4 * e], acc[i]);
+          for (int e = 0; e < E; ++e) s = dot4(w[g][e], *(const f32x4*)&in[min(b + i, nb - 1) * K + k + 4 * e], s);
+          acc[i] = in_row ? s : acc[i];
+        }
       }
       wave_sums(acc);
       float v = acc[0];

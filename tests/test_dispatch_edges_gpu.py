@@ -105,6 +105,29 @@ def test_cond_embed_edges(dtype, hidden, dh, batch):
     check("cond", g.host(out), ref, None, 4e-6)
 
 
+# An infinite hidden value in the last columns of a row: the lanes past the
+# row's end, which re-read them, must not add 0 x inf = NaN.  One sample and
+# several (the two layouts of the output layer), rows that end inside, at and a
+# whole group of columns before the end of the registers' range.
+@pytest.mark.parametrize("dtype,hidden,dh,batch", [("bf16", 64, 64, 1), ("bf16", 1152, 72, 1), ("bf16", 1152, 72, 3),
+                                                   ("f32", 1280, 64, 2), ("f32", 1344, 64, 1), ("bf16", 3072, 128, 5)])
+def test_cond_embed_infinite_hidden_value(dtype, hidden, dh, batch):
+    import paper_2605_25550_amd as dm
+    g = _gpu()
+    cfg = synth.CONFIGS["c1"].with_(dtype=dtype, hidden=hidden, heads=hidden // dh, head_dim=dh, batch=batch, tokens=1,
+                                    n_blocks=1, n_classes=30, mlp_hidden=64)
+    sw = synth.step_weights(cfg)
+    sw["b_t1"][-2] = np.inf  # SiLU(inf) = inf
+    sw["w_t2"][:, -2] = np.where(np.arange(hidden) % 2, 0.5, -0.25)
+    shape = dm.shape_of(cfg)
+    w = {k: g.dev(sw[k], dm.weight_dtype(shape)) for k in ("w_t1", "b_t1", "w_t2", "b_t2", "class_table")}
+    t, y = g.dev(np.linspace(0.0, 999.0, batch)), torch.zeros(batch, dtype=torch.int32, device="cuda")
+    out = torch.zeros((batch, hidden), device="cuda")
+    dm.cond_embed(shape, t, y, w, out, dm.alloc_workspace(shape, dm.DIT_WS_COND))
+    want = np.broadcast_to(np.where(np.arange(hidden) % 2, np.inf, -np.inf), (batch, hidden))
+    assert np.array_equal(g.host(out), want)
+
+
 # Small grids (one round of 64 x 32, 64 x 64, 64 x 96 or 64 x 128 tiles, k-ranges
 # with the residual reduction): hidden 64 (fewer k-slices than k-groups),
 # ragged rows, tiles that straddle samples, q/k padding of head_dim 72, v^T
