@@ -689,7 +689,9 @@ __global__ __launch_bounds__(256) void patch_mfma_kernel(int rows, int T, int P,
                                                          const float* __restrict__ pos, float* __restrict__ x) {
   constexpr int RT = PM_ROWS / 16;
   const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
-  const int n0 = blockIdx.x * 64, row0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * PM_ROWS;
+  // column blocks fastest, in one dimension: the row blocks can exceed the 65536 of a grid's second
+  const int cb = D >> 6, rb = blockIdx.x / cb;
+  const int n0 = (blockIdx.x - rb * cb) * 64, row0 = (rb * 4 + (threadIdx.x >> 6)) * PM_ROWS;
   if (row0 >= rows) return;
   const WT* wr = w + (long)(n0 + 16 * (r16 >> 2) + (r16 & 3)) * P + 4 * kq;  // tile j: + 4 j rows
   const float* zr[RT];
@@ -748,8 +750,8 @@ static void launch_patch_embed_t(int rows, int T, int P, int D, const float* z, 
   // and latents and weights aligned for it (the entry points ask for 4 bytes only)
   const bool mfma = P % 16 == 0 && (uintptr_t)z % 16 == 0 && (uintptr_t)w % (4 * sizeof(WT)) == 0;
   if (mfma)
-    hipLaunchKernelGGL((patch_mfma_kernel<WT>), dim3(D / 64, (rows + 4 * PM_ROWS - 1) / (4 * PM_ROWS)), dim3(256), 0,
-                       st, rows, T, P, D, z, w, b, pos, x);
+    hipLaunchKernelGGL((patch_mfma_kernel<WT>), dim3(D / 64 * ((rows + 4 * PM_ROWS - 1) / (4 * PM_ROWS))), dim3(256),
+                       0, st, rows, T, P, D, z, w, b, pos, x);
   else if (P <= 16)
     hipLaunchKernelGGL((patch_row_kernel<WT>), dim3(rows), dim3(256), 0, st, T, P, D, z, w, b, pos, x);
   else

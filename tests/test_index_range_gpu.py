@@ -1,6 +1,7 @@
-"""GPU parity at the upper end of the index ranges: operands whose byte
-offsets pass 2^32, against the fp64 oracle on the rows and weights that lie
-there.  Metric and fp32 bar as in test_dispatch_edges_gpu.py."""
+"""GPU parity at the upper end of the index ranges (operands whose byte offsets
+pass 2^32, grids beyond 65536 blocks of rows) against the fp64 oracle, on the
+rows and weights that lie there.  Metric and fp32 bar as in
+test_dispatch_edges_gpu.py."""
 import numpy as np
 import pytest
 import torch
@@ -58,3 +59,22 @@ def test_f32_weights_past_four_gib():
                      dm.alloc_workspace(shape, dm.DIT_WS_BLOCK))
     ref = O.dit_block(inp["x"], inp["cond"], f64(w["img"]), cfg.heads, cfg.ln_eps)
     check("img", g.host(x), ref, inp["x"], 2e-5)
+
+
+def test_patch_embed_of_nine_million_rows():
+    """16 channels, more than 65536 blocks of 128 rows: the last sample of a step
+    against the oracle."""
+    import paper_2605_25550_amd as dm
+    from tests.test_parity_gpu import TOL, step_ref
+    cfg = _cfg(batch=8200, tokens=1024, mlp_hidden=64).with_(dtype="bf16", grid=None, patch_in=16, patch_out=4)
+    assert cfg.batch * cfg.tokens > 65536 * 128
+    g = _gpu()
+    sw, blocks, inp = synth.step_weights(cfg), [synth.block_weights(cfg, 0)], synth.inputs(cfg.with_(batch=1))
+    ds = g.DeviceStep(cfg, blocks, sw)
+    z = torch.zeros(cfg.batch, cfg.tokens, 16, device="cuda")
+    c = torch.zeros(cfg.batch, cfg.hidden, device="cuda")
+    z[-1], c[-1] = g.dev(inp["patches"])[0], g.dev(inp["cond"])[0]
+    out = torch.empty(cfg.batch, cfg.tokens, 4, device="cuda")
+    dm.step_forward(ds.shape, ds.table, z, c, out, ds.ws)
+    ref, _ = step_ref(cfg, sw, blocks, inp, None, inp["cond"])
+    check("step", g.host(out[-1:]), ref, None, TOL["bf16"])
