@@ -88,12 +88,14 @@ struct Layout {
 };
 
 // *split: k-ranges of the last problem (0: none), negative: of both problems.
-int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids = true);
+int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split);
 
-// Bytes of fp32 partials the split GEMMs of this shape need (the largest of
-// the output projection, fc1 and fc2; 0 if none is split).  The small-grid
-// tiles choose their ranges within what the larger tiles' rules need.
-static size_t split_part_bytes(const dit_shape* s) {
+// Bytes of fp32 partials that the split GEMMs of this shape need (the largest
+// of the output projection, fc1 and fc2; 0 if none is split), not counting
+// - fc2's where they fit `span_o`, the q, k, v and o regions, dead by then;
+// - whole splits (256 x 128 tiles; tail splits of that size have two problems
+//   and a positive split): those take what the dead regions hold.
+static size_t split_part_bytes(const dit_shape* s, size_t span_o) {
   if (s->dtype != DIT_BF16) return 0;
   const int ns = s->text_tokens > 0 ? 2 : 1;
   const int D = s->hidden, F = s->mlp_hidden;
@@ -108,8 +110,10 @@ static size_t split_part_bytes(const dit_shape* s) {
       p[i].hidden = D;
     }
     int S = 0;
-    choose_tile(p, ns, g[0], SIZE_MAX, &S, false);
+    const int cfg = choose_tile(p, ns, g[0], SIZE_MAX, &S);
+    if (cfg == TILE_256x128 && (S < 0 || ns == 1)) continue;
     const size_t b = (size_t)S * p[ns - 1].M * p[ns - 1].N * 4;
+    if (g[0] == EPI_RESID2 && b <= span_o) continue;
     if (b > need) need = b;
   }
   return need;
@@ -147,7 +151,7 @@ Layout layout(const dit_shape* s, int kind) {
   L.o = take(rows * D * E);
   L.g = take(rows * F * E);
   {
-    const size_t need = split_part_bytes(s), span = L.o - L.q;
+    const size_t need = split_part_bytes(s, L.g - L.q), span = L.o - L.q;
     L.part = need <= span ? L.q : take(need);
     L.part_cap = need <= span ? span : need;
   }
@@ -267,31 +271,6 @@ static int tail_split(const GemmProb* p, int np, int epi, int bm, int bn, size_t
 // of a round.
 static double tail_rounds(long t0, int S) { return (double)(t0 / 256) + 1.0 / S + 0.15; }
 
-// Fill split, which sizes the partials of small grids in the workspace
-// (split_part_bytes); the ranges are chosen within that size by small_grid and
-// whole_split.  A single problem whose tiles cannot fill the GPU in S equal
-// k-ranges of at least 4 slices, e.g. the DiT-XL/2 fc2 at one sample of 256
-// tokens: 36 tiles of 64 x 128, each 72 k-slices long, as 216 units of 12.  Up
-// to 128 tiles the units are at most one per CU, up to half of `slots` (the
-// workgroups resident at once) they may fill the slots.  S is the largest
-// such split for which the estimated gain
-//   (1 - 1/S) * 0.45 us per slice - partial traffic at 5 TB/s - 3 us
-// of reduction launch is positive.  Returns S (0: no split).
-static int fill_split(const GemmProb& p, int epi, int bm, int bn, long slots, size_t part_cap) {
-  if ((epi != EPI_GELU && epi != EPI_RESID && epi != EPI_RESID2) || part_cap == 0) return 0;
-  const long t = (long)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
-  const int ks = p.K / 64;
-  if (t == 0 || 2 * t > slots) return 0;
-  const long units = t <= 128 ? 256 : slots;
-  for (int S = 8; S >= 2; --S) {
-    if (t * S > units || ks % S != 0 || ks / S < 4 || (size_t)S * p.M * p.N * 4 > part_cap) continue;
-    const double mn = (double)p.M * p.N;
-    const double gain_us = (1.0 - 1.0 / S) * ks * 0.45 - (S * 4.0 + 8.0) * mn / 5e6 - 3.0;
-    if (gain_us > 0) return S;
-  }
-  return 0;
-}
-
 // Small grids: a call that fits one round of at most 256 workgroups is bound
 // by a workgroup's chain of slice loads, the same rate for every tile
 // measured (K 384..4608, 64..512 rows): 4.2 us + 11.5 us per MB of operand rows
@@ -357,7 +336,7 @@ static int whole_split(const GemmProb* p, int np, int epi, size_t part_cap) {
   return 0;
 }
 
-int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split, bool small_grids) {
+int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split) {
   *split = 0;
   long t128 = 0, t144 = 0, t256 = 0, t2x1 = 0, t192 = 0;
   bool n144 = true, ok256 = true, ok128 = true, ok192 = epi != EPI_RESID && epi != EPI_RESID2;
@@ -393,28 +372,16 @@ int choose_tile(const GemmProb* p, int np, int epi, size_t part_cap, int* split,
       return best;
     }
   }
-  if (small_grids) {
-    const int cfg = small_grid(p, np, epi, part_cap, split);
-    if (cfg >= 0) return cfg;
-    const int S = whole_split(p, np, epi, part_cap);
-    if (S) {
-      *split = np == 2 ? -S : S;  // negative: both problems
-      return TILE_256x128;
-    }
+  const int small = small_grid(p, np, epi, part_cap, split);
+  if (small >= 0) return small;
+  const int S = whole_split(p, np, epi, part_cap);
+  if (S) {
+    *split = np == 2 ? -S : S;  // negative: both problems
+    return TILE_256x128;
   }
-  const int cfg = ((t128 >= 256 && t128 < 512) || t128 >= 768) ? TILE_128x128
-                  : t128 >= 512                                   ? TILE_64x128_S2
-                                                                  : TILE_64x128;
-  // With small_grids, grids that fill_split could split (tiles <= slots / 2)
-  // have been taken by the rules above.
-  if (np == 1 && !small_grids) {
-    int bm = 0, bn = 0;
-    gemm_tile_dims(cfg, &bm, &bn);
-    // resident workgroups per CU (LDS): 128x128 and 64x128 with 3 slots two, 64x128 with 2 slots three
-    const long per_cu = cfg == TILE_64x128_S2 ? 3 : 2;
-    *split = fill_split(p[0], epi, bm, bn, 256 * per_cu, part_cap);
-  }
-  return cfg;
+  return ((t128 >= 256 && t128 < 512) || t128 >= 768) ? TILE_128x128
+         : t128 >= 512                                   ? TILE_64x128_S2
+                                                         : TILE_64x128;
 }
 
 // Row tail: a single problem of whole rounds of 256-row tiles plus a short
@@ -531,8 +498,8 @@ hipError_t run_gemm(Gemm& G, int dtype, hipStream_t st) {
     tcfg = f32_plan(a.p, a.nprob, G.epi, G.part_cap, &split);
     gemm_f32_tile_dims(tcfg, &bm, &bn);
   }
-  // Split problems: the second of two (tail schedule), the only one (fill
-  // split, every unit in one round, the usual tile order) or both.
+  // Split problems: the second of two (tail schedule), the only one (every
+  // unit in one round, the usual tile order) or both.
   const bool both = split < 0;
   if (both) split = -split;
   const int sp = both ? 0 : a.nprob - 1;  // the first split problem
