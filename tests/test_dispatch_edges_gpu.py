@@ -143,18 +143,26 @@ def test_small_grid_edges(hidden, dh, batch, t, tt):
     block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=4 * hidden))
 
 
-# Steps whose residual GEMMs are split: their reductions do the LayerNorms in
-# between, the next block's and the final one (hidden 192: one 4-column group
-# per thread, 1152: two, 2304: three of four); a sequence of blocks against the
-# same blocks called one by one, each of which ends without a LayerNorm.
-@pytest.mark.parametrize("dtype,hidden,dh,batch,t", [("bf16", 192, 64, 1, 40), ("bf16", 1152, 72, 1, 200),
-                                                     ("bf16", 1152, 72, 2, 77), ("bf16", 2304, 72, 1, 65),
-                                                     ("f32", 1152, 72, 2, 333)])
-def test_step_with_split_residuals(dtype, hidden, dh, batch, t):
+# Steps whose residual GEMMs are split: their reductions do the LayerNorms that
+# follow, the next block's and the final one after fc2 (hidden 192 and 576: one
+# 4-column group per thread, 1152: two, 2304: three of four) and, where it is
+# split too (hidden 2560), the one after the output projection.  `lns` of the
+# five LayerNorms of two blocks and the final layer remain launches of their own.
+@pytest.mark.parametrize("dtype,hidden,dh,mlp,batch,t,lns", [
+    ("bf16", 192, 64, 3072, 1, 40, 3), ("bf16", 576, 72, 2304, 3, 85, 3), ("bf16", 1152, 72, 4608, 1, 200, 3),
+    ("bf16", 1152, 72, 4608, 2, 77, 3), ("bf16", 2304, 72, 9216, 1, 65, 3), ("bf16", 2560, 128, 2560, 1, 17, 1),
+    ("f32", 576, 72, 2304, 1, 33, 3), ("f32", 1152, 72, 4608, 2, 333, 3)])
+def test_step_with_split_residuals(dtype, hidden, dh, mlp, batch, t, lns):
+    import paper_2605_25550_amd as dm
     g = _gpu()
-    cfg = _cfg(dtype, hidden, dh, batch=batch, tokens=t, mlp_hidden=4 * hidden).with_(n_blocks=2, grid=None)
+    cfg = _cfg(dtype, hidden, dh, batch=batch, tokens=t, mlp_hidden=mlp).with_(n_blocks=2, grid=None)
     sw, blocks, inp = synth.step_weights(cfg), [synth.block_weights(cfg, l) for l in range(2)], synth.inputs(cfg)
-    out, _ = g.DeviceStep(cfg, blocks, sw).run(inp["patches"], inp["cond"])
+    ds = g.DeviceStep(cfg, blocks, sw)
+    dm.timing_enable("ln_mod", 16)
+    out, _ = ds.run(inp["patches"], inp["cond"])
+    launches = dm.timing_read()[1]
+    dm.timing_disable()
+    assert launches == lns
     from tests.test_parity_gpu import step_ref
     ref, _ = step_ref(cfg, sw, blocks, inp, None, inp["cond"])
     check("step", out, ref, None, TOL[dtype])
@@ -201,12 +209,22 @@ def test_patch_embed_edges(dtype, hidden, dh, batch, grid, p, shift):
     check("step", g.host(out), ref, None, TOL[dtype])
 
 
-# Residual GEMMs whose k-ranges cover both streams: fc2 of the joint block at
-# 1900 + 140 rows (64 256 x 128 tiles would be a quarter round), and one stream.
-@pytest.mark.parametrize("hidden,dh,f,batch,t,tt", [(1024, 64, 6144, 2, 1900, 70), (1536, 64, 6144, 2, 1000, 77),
-                                                    (1536, 128, 6144, 1, 2100, 0)])
-def test_whole_split_edges(hidden, dh, f, batch, t, tt):
+# fc2 as 256 x 128 tiles in S k-ranges over the whole problem: both streams of a
+# joint block (in three ranges beside fc1's text stream in two, the tail
+# schedule; in two), and one stream.  The reductions' bytes show the ranges.
+@pytest.mark.parametrize("hidden,dh,f,batch,t,tt,S,tail", [(768, 64, 6144, 2, 1000, 512, 3, 2),
+                                                           (1536, 64, 6144, 2, 1000, 77, 2, 0),
+                                                           (1536, 128, 6144, 1, 2100, 0, 2, 0)])
+def test_whole_split_edges(hidden, dh, f, batch, t, tt, S, tail):
+    import paper_2605_25550_amd as dm
+    dm.timing_enable("other", 16)
     block_case(_cfg("bf16", hidden, dh, batch=batch, tokens=t, text_tokens=tt, mlp_hidden=f))
+    _, launches, _, nbytes = dm.timing_read()
+    dm.timing_disable()
+    # SiLU(c) is computed by adaLN's workgroups: the reductions are all there is
+    assert launches == (2 if tt else 1) + (1 if tail else 0)
+    want = sum(batch * n * hidden * (4 * S + 8) + 2 * hidden for n in (t, tt) if n)
+    assert nbytes == want + (batch * tt * f * (4 * tail + 2) + 2 * f if tail else 0)
 
 
 # Keys split over the waves: a wave whose only key scores -inf against every
