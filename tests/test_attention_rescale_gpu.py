@@ -1,10 +1,11 @@
 """GPU parity of attention's lazy max against the fp64 oracle.
 
-The kernels keep the softmax's running max m_run fixed after the first key
-tile and move it (rescaling O, l and the tile's scores) only when a tile's
-scores lead it by more than 2^64 in the exp2 domain.  Ordinary inputs never
-take that branch after the first tile, and their first tile's max sits near
-zero; both cases are forced here:
+The pipelined and the four-wave kernel keep the softmax's running max m_run
+fixed after the first key tile and move it (rescaling O, l and the tile's
+scores) only when a tile's scores lead it by more than 2^64 in the exp2 domain;
+the kernel that splits the keys over its waves moves it with every tile.
+Ordinary inputs never take that branch after the first tile, and their first
+tile's max sits near zero; both cases are forced here:
 
 - a move mid-sequence: the tokens of the first key tiles and those after a
   boundary lie along two different directions, the k projection is set equal
@@ -89,20 +90,26 @@ def _cfg(kind):
         "pipe_dh72_fold_long": synth.CONFIGS["c1"].with_(batch=6, tokens=600, n_blocks=1),
         "pipe_dh64_long": synth.CONFIGS["c1"].with_(batch=6, tokens=600, hidden=1024, heads=16, head_dim=64,
                                                     mlp_hidden=512, n_blocks=1),
-        # small grids: the four-wave kernel
+        # fewer items and keys, but more than 256 workgroups of 32 queries: the four-wave kernel
+        "four_dh128": synth.CONFIGS["c1"].with_(batch=7, tokens=150, hidden=1024, heads=8, head_dim=128,
+                                                mlp_hidden=512, n_blocks=1),
+        "four_dh72_fold": synth.CONFIGS["c1"].with_(batch=4, tokens=150, n_blocks=1),
+        "four_dh64": synth.CONFIGS["c1"].with_(batch=4, tokens=150, hidden=1024, heads=16, head_dim=64,
+                                               mlp_hidden=512, n_blocks=1),
+        # small grids: keys split over the waves, each with a running max of its own
         "small_dh128": synth.CONFIGS["c1"].with_(batch=2, tokens=150, hidden=256, heads=2, head_dim=128,
                                                  mlp_hidden=512, n_blocks=1),
-        "small_dh72_fold": synth.CONFIGS["c1"].with_(batch=2, tokens=150, hidden=576, heads=8, head_dim=72,
-                                                     mlp_hidden=256, n_blocks=1),
+        "small_dh72": synth.CONFIGS["c1"].with_(batch=2, tokens=150, hidden=576, heads=8, head_dim=72,
+                                                mlp_hidden=256, n_blocks=1),
     }[kind]
 
 
 # (case, q/k scale): the least power of two that moves the max for most later queries
-MOVE = [("pipe_dh128", 4.0), ("pipe_dh72_fold", 4.0), ("pipe_dh64", 8.0), ("small_dh128", 8.0),
-        ("small_dh72_fold", 8.0)]
+MOVE = [("pipe_dh128", 4.0), ("pipe_dh72_fold", 4.0), ("pipe_dh64", 8.0), ("four_dh128", 4.0), ("four_dh72_fold", 4.0),
+        ("four_dh64", 8.0), ("small_dh128", 8.0), ("small_dh72", 8.0)]
 # (case, q/k scale, amplitude): first tiles far below zero for some later queries
 LOW = [("pipe_dh128", 4.0, 20.0), ("pipe_dh72_fold", 4.0, 20.0), ("pipe_dh64", 8.0, 6.0),
-       ("small_dh72_fold", 8.0, 6.0)]
+       ("four_dh128", 4.0, 20.0), ("four_dh72_fold", 4.0, 20.0), ("four_dh64", 8.0, 6.0), ("small_dh72", 8.0, 6.0)]
 
 
 MOVE_LONG = [("pipe_dh128_long", 4.0), ("pipe_dh72_fold_long", 4.0), ("pipe_dh64_long", 8.0)]

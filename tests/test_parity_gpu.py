@@ -76,21 +76,22 @@ SMALL = [
     ("bf16_joint_dh72_tt5", synth.CONFIGS["c3"].with_(batch=1, tokens=64, text_tokens=5, hidden=576, heads=8,
                                                       head_dim=72, mlp_hidden=256, n_blocks=1)),
     # DiT-XL widths with ragged row counts that select the 256-row GEMM tiles:
-    # 2000 rows -> QKV 256x128, fc1 256x256, out/fc2 64x144 (last M tile ragged)
+    # 2000 rows -> QKV 256x128, fc1 256x192, out/fc2 64x144 (last M tile ragged)
     ("bf16_xl_t250_b8_tiles", synth.CONFIGS["c1"].with_(batch=8, tokens=250, n_blocks=1)),
     # 4096 rows at hidden 576 and MLP 1728 (both multiples of 144, 9 and 27
     # k-slices): the output projection and fc2 take the 64x144 tiles with a
     # single k-group (odd slice count)
     ("bf16_144_one_kgroup", synth.CONFIGS["c1"].with_(batch=4, tokens=1024, hidden=576, heads=8, head_dim=72,
                                                       mlp_hidden=1728, n_blocks=1)),
-    # DiT-XL widths at one or two samples: the output projection and fc2 run
-    # too few 64x128 tiles to fill the GPU and are split into k-ranges
-    # (fc2 at 256 rows: 36 tiles x 6 ranges; 250 rows: a ragged row tile)
+    # DiT-XL widths at one or two samples: fc2 runs too few 64x128 tiles to
+    # fill the GPU and is split into k-ranges (256 rows: 36 tiles x 6 ranges,
+    # 512: 72 x 3; 250 rows: a ragged row tile); at four samples it is whole
     ("bf16_xl_b1_split", synth.CONFIGS["c1"].with_(batch=1, n_blocks=1)),
     ("bf16_xl_b1_t250_split", synth.CONFIGS["c1"].with_(batch=1, tokens=250, n_blocks=1)),
     ("bf16_xl_b2_split", synth.CONFIGS["c1"].with_(batch=2, n_blocks=1)),
-    ("bf16_xl_b4_split", synth.CONFIGS["c1"].with_(batch=4, n_blocks=1)),
-    # 2340 rows -> QKV (incl. the v^T columns) and fc1 on 256x256 tiles
+    ("bf16_xl_b4", synth.CONFIGS["c1"].with_(batch=4, n_blocks=1)),
+    # 2340 rows -> QKV (incl. the v^T columns) and fc1 on 256x192 tiles, fc2 as
+    # 256x128 tiles in two k-ranges
     ("bf16_xl_t260_b9_tiles", synth.CONFIGS["c1"].with_(batch=9, tokens=260, n_blocks=1)),
     # 600 rows (and 512 + 64 joint rows) at widths that are multiples of 144:
     # the QKV projection takes the 64x144 tiles, whose 48-column wave strips
@@ -99,9 +100,10 @@ SMALL = [
     ("bf16_qkv_144_dh72", synth.CONFIGS["c1"].with_(batch=2, tokens=300, n_blocks=1)),
     ("bf16_joint_qkv_144", synth.CONFIGS["c3"].with_(batch=1, tokens=512, text_tokens=64, hidden=1152, heads=9,
                                                      head_dim=128, mlp_hidden=1024, n_blocks=1)),
-    # >= 256 (sample, head, 256-query) items select the software-pipelined
-    # attention kernel: one, two and three key tiles, ragged last tiles
-    ("bf16_pipe_dh64_t17_b16", synth.CONFIGS["c1"].with_(batch=16, tokens=17, hidden=1024, heads=16, head_dim=64,
+    # >= 256 (sample, head, 256-query) items and more than 256 workgroups of 32
+    # queries select the software-pipelined attention kernel: one, two and three
+    # key tiles, ragged last tiles
+    ("bf16_pipe_dh64_t17_b17", synth.CONFIGS["c1"].with_(batch=17, tokens=17, hidden=1024, heads=16, head_dim=64,
                                                          mlp_hidden=512, n_blocks=1)),
     ("bf16_pipe_dh128_t100_b32", synth.CONFIGS["c1"].with_(batch=32, tokens=100, hidden=1024, heads=8, head_dim=128,
                                                            mlp_hidden=512, n_blocks=1)),
@@ -172,8 +174,9 @@ def test_cond_embed_and_pos_table():
 # ------------------------------------------------------------------ step (small)
 STEP_SMALL = [
     ("fp32_step_l2", synth.CONFIGS["c0"].with_(n_blocks=2, batch=2, tokens=64, grid=(8, 8))),
-    # patch embeddings of 80 and 150 channels: the tiled patch kernel's full
-    # 64-channel chunks plus a partial one, and a ragged last row block
+    # patch embeddings of 80 channels (matrix cores: a full and a partial
+    # 64-channel pass) and of 150 and 33 (the tiled kernel's full 64-channel
+    # chunks plus a partial one), with a ragged last row block
     ("bf16_step_patch80", synth.CONFIGS["c4"].with_(n_blocks=1, batch=1, tokens=100, hidden=256, heads=2, head_dim=128,
                                                     mlp_hidden=512, patch_in=80, patch_out=80)),
     ("bf16_step_patch150_b2", synth.CONFIGS["c4"].with_(n_blocks=1, batch=2, tokens=45, hidden=512, heads=4,
