@@ -33,24 +33,23 @@ PEAK_HBM_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_2605_25550_amd", "csrc")
 PROFILES = os.path.join(ROOT, "profiles")
 
-# kernel class -> (regex of its kernel symbol in rocprofv3 output, source file).  The
-# GEMM classes differ in the last template argument (the fused epilogue), for
-# both GEMM kernels (gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, EPI>,
-# gemm_bf16_144_kernel<EPI>).
+# kernel class -> (regex of its kernel symbol in rocprofv3 output, source files).  The
+# GEMM classes differ in the template argument of the fused epilogue, for all
+# GEMM kernels (gemm_bf16_kernel<BM, BN, WGM, WGN, STAGES, EPI>,
+# gemm_bf16_144_kernel<EPI, KG>, gemm_bf16_kg_kernel<WGM, WGN, KG, TM, TN, ST, EPI>).
 def _gemm_re(epi: int) -> str:
-    # generic kernel: epilogue is the last of six template arguments; the
-    # 64x144 kernel: <epilogue, k-groups>
-    return rf"gemm_bf16_(?:kernel<(?:\d+, ){{5}}{epi}>|144_kernel<{epi}, \d+>)"
+    return rf"gemm_bf16_(?:kernel<(?:\d+, ){{5}}{epi}>|144_kernel<{epi}, \d+>|kg_kernel<(?:\d+, ){{6}}{epi}>)"
 
 
+_GEMM_SRC = ("gemm_bf16.hip", "gemm_bf16_kg.hip")
 CLASSES = {
-    "gemm_qkv": (_gemm_re(0), "gemm_bf16.hip"),
-    "attention": (r"attn_bf16_\w*kernel<", "attention_bf16.hip"),
-    "gemm_out": (_gemm_re(2), "gemm_bf16.hip"),
-    "gemm_fc1": (_gemm_re(1), "gemm_bf16.hip"),
-    "gemm_fc2": (_gemm_re(4), "gemm_bf16.hip"),
-    "ln_mod": (r"ln_mod_kernel<", "elementwise.hip"),
-    "adaln": (r"adaln\w*_kernel", "elementwise.hip"),
+    "gemm_qkv": (_gemm_re(0), _GEMM_SRC),
+    "attention": (r"attn_bf16_\w*kernel<", ("attention_bf16.hip",)),
+    "gemm_out": (_gemm_re(2), _GEMM_SRC),
+    "gemm_fc1": (_gemm_re(1), _GEMM_SRC),
+    "gemm_fc2": (_gemm_re(4), _GEMM_SRC),
+    "ln_mod": (r"ln_mod_kernel<", ("elementwise.hip",)),
+    "adaln": (r"adaln\w*_kernel", ("elementwise.hip",)),
 }
 
 
@@ -95,9 +94,9 @@ def progress(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def source_hash(fname: str) -> str:
+def source_hash(files) -> str:
     h = hashlib.sha256()
-    for f in (fname, "common.h", "kernels.h"):
+    for f in (*files, "common.h", "kernels.h"):
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -41,6 +41,20 @@ def test_algorithmic_flops_other_mlp_width():
     assert bench.algorithmic_flops(c) == pytest.approx(expect, rel=1e-12)
 
 
+@pytest.mark.parametrize("cls,epi", [("gemm_qkv", 0), ("gemm_fc1", 1), ("gemm_out", 2), ("gemm_fc2", 4)])
+def test_gemm_classes_cover_every_gemm_kernel(cls, epi):
+    """Each class has the three GEMM kernels' instances of its epilogue only
+    (the final layer's is none of them), and its records go stale with either
+    source."""
+    import re
+    rx, src = bench.CLASSES[cls]
+    for e in range(5):
+        for name in (f"gemm_bf16_kernel<256, 128, 4, 2, 3, {e}>", f"gemm_bf16_144_kernel<{e}, 2>",
+                     f"gemm_bf16_kg_kernel<2, 1, 4, 2, 2, 3, {e}>"):
+            assert bool(re.search(rx, f"void ditmi::{name}(ditmi::GemmArgs)")) == (e == epi), name
+    assert {"gemm_bf16.hip", "gemm_bf16_kg.hip"} == set(src)
+
+
 def test_traffic_record_only_for_the_current_source(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "PROFILES", str(tmp_path))
     rec = {"kernel_class": "attention", "workload": "w", "hbm_bytes_per_launch": 123.0,
