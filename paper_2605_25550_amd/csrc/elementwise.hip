@@ -224,7 +224,11 @@ hipError_t launch_splitk_resid_ln(const float* part, int S, int M, int N, const 
 // waves (28 matrices: 167 us).
 //
 // SiLU(c): FUSED, every workgroup computes it into LDS for up to nbc samples
-// at a time and one launch fewer is needed (adaln_fused).  Otherwise (bf16
+// at a time and one launch fewer is needed (adaln_fused).  In fp32 each further
+// pass of what 64 KB hold reads the matrix again, from hidden 3072 on slower than
+// the VALU kernel it replaced (8 samples: 120 -> 147 us; 4096 160 -> 230; one sample
+// 58 -> 52, 90 -> 88); 132 KB helped only where it saved the one further pass
+// (2048: 67 -> 48) and cost residency elsewhere (3072: 153).  Otherwise (bf16
 // only) it comes from `act`, written once by silu_bf16_kernel and read through
 // L2 with the weights.  Lanes of samples past the batch supply zeros.  D
 // lanes hold sample lane % 16, rows 4 (lane / 16) + i.
@@ -482,7 +486,10 @@ __global__ __launch_bounds__(1024) void cond_hidden_kernel(int B, int N, const f
 // 4 E consecutive weights per lane, 256 E apart).  NS = 4: h1 of up to nbc
 // samples at a time staged in LDS, four samples per pass, E = 1 (conflict-free
 // reads); NS = 1 (one sample): read straight from global memory with the
-// weights, E = 2 (16-byte loads of bf16 weights).
+// weights, E = 2 (16-byte loads of bf16 weights).  Lanes past a row's end
+// must add nothing, whatever they read (zero weights would make NaN of an
+// infinity): their sums are dropped.  They read on past a staged row, which costs
+// less than a clamped address: hs has room for 256 G floats from its last row on.
 template <typename WT, int G, int E, int NW, int NS>
 __global__ __launch_bounds__(NW * 64) void cond_out_kernel(int B, int N, int K, int nbc, const float* h1, const WT* W,
                                                            const WT* bias, const WT* table, const int32_t* y,
@@ -519,15 +526,13 @@ __global__ __launch_bounds__(NW * 64) void cond_out_kernel(int B, int N, int K, 
       float acc[NS] = {};
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        // lanes past the row's end add nothing (zero weights would not do: 0 x inf)
-        const bool in_row = (256 * g + lane * 4) * E < K;
-        const int k = in_row ? (256 * g + lane * 4) * E : K - 4 * E;
+        const int kl = (256 * g + lane * 4) * E, k = NS > 1 ? kl : min(kl, K - 4 * E);
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
           float s = acc[i];
 #pragma unroll
           for (int e = 0; e < E; ++e) s = dot4(w[g][e], *(const f32x4*)&in[min(b + i, nb - 1) * K + k + 4 * e], s);
-          acc[i] = in_row ? s : acc[i];
+          acc[i] = kl < K ? s : acc[i];
         }
       }
       wave_sums(acc);
@@ -547,14 +552,22 @@ static hipError_t cond_launch_t(int B, int D, const float* t, float t_val, const
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // h1 of as many samples as 64 KB hold (at least 4: hidden <= 4096), one lane
-  // each at most.  4 rows per workgroup fill the GPU soonest; 16 where staging
-  // the samples for every 4 rows would be the larger part of the work (11
-  // samples at hidden 3072, fp32: 34 us with 4 rows, 23 with 16).
+  // each at most, and what the lanes past the last row's end read (at most 11 KB).
+  // 4 rows per workgroup fill the GPU soonest; 16 where staging the samples for
+  // every 4 rows would be the larger part of the work (11 samples at hidden 3072,
+  // fp32: 34 us with 4 rows, 23 with 16).
+  const int past = ((D <= 1280 ? 5 : 16) * 256 - D) * 4;
   const int nbc = std::min(std::min(B, 64), 64 * 1024 / (D * 4));
-  const size_t lds = B > 1 ? (size_t)nbc * D * 4 : 0;
+  const size_t lds = B > 1 ? (size_t)nbc * D * 4 + past : 0;
 #define COND_OUT(G, E, NW, NS)                                                                                       \
-  hipLaunchKernelGGL((cond_out_kernel<WT, G, E, NW, NS>), dim3(D / NW), dim3(NW * 64), lds, st, B, D, D, nbc, h1, w2, \
-                     b2, table, y, cond)
+  do {                                                                                                               \
+    if (lds > 64 * 1024 &&                                                                                           \
+        (e = hipFuncSetAttribute((const void*)cond_out_kernel<WT, G, E, NW, NS>,                                     \
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, 76 * 1024)) != hipSuccess)              \
+      return e;                                                                                                      \
+    hipLaunchKernelGGL((cond_out_kernel<WT, G, E, NW, NS>), dim3(D / NW), dim3(NW * 64), lds, st, B, D, D, nbc, h1,  \
+                       w2, b2, table, y, cond);                                                                      \
+  } while (0)
   const bool wide = (size_t)B * D * 4 > 40 * 1024;
   if (D <= 1280) {  // 5 x 256 weights per row
     if (B == 1) COND_OUT(3, 2, 4, 1);

@@ -110,7 +110,8 @@ def test_cond_embed_edges(dtype, hidden, dh, batch):
 # several (the two layouts of the output layer), rows that end inside, at and a
 # whole group of columns before the end of the registers' range.
 @pytest.mark.parametrize("dtype,hidden,dh,batch", [("bf16", 64, 64, 1), ("bf16", 1152, 72, 1), ("bf16", 1152, 72, 3),
-                                                   ("f32", 1280, 64, 2), ("f32", 1344, 64, 1), ("bf16", 3072, 128, 5)])
+                                                   ("f32", 1280, 64, 2), ("f32", 1344, 64, 1), ("f32", 1344, 64, 13),
+                                                   ("bf16", 2048, 128, 8), ("bf16", 3072, 128, 5)])
 def test_cond_embed_infinite_hidden_value(dtype, hidden, dh, batch):
     import paper_2605_25550_amd as dm
     g = _gpu()
