@@ -15,7 +15,8 @@
 // keys of every 16-key group stored in the order of that permutation,
 // kernels.h v_key_pos), so its A operand is one 16-byte LDS read per lane.
 //
-// Schedule.  A workgroup is 8 waves (256 queries; 4 waves for small grids),
+// Schedule.  A workgroup is 8 waves (256 queries; 4 waves for smaller grids; the
+// smallest split the keys over the waves of 32 queries, attn_bf16_split_kernel),
 // two waves per SIMD, so one wave's softmax VALU work runs while the other's
 // MFMAs are in the matrix pipe.  K and V^T tiles of 64 keys are copied
 // HBM -> LDS by the global_load_lds_dwordx4 DMA path into a ring of 3 slots,
@@ -996,13 +997,16 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, hipStream_t st) {
   //   16 heads of 72: 256 tokens 5.7 against 9.0 for the four-wave kernel, 512
   //   7.2 against 13.4, 1024 (512 workgroups) 19.4 against 22.1 for the
   //   pipelined one; 384 workgroups at 256 tokens 10.4 against 9.0; head_dim 128,
-  //   512 workgroups at 1000 tokens 33.0 against 31.2);
+  //   512 workgroups at 1000 tokens 33.0 against 31.2; few heads and long, 1 x 16000
+  //   tokens of 64: 222 against 280 for the four-wave kernel, 6 x 2700 37 against 53);
   // - 256 items of 256 queries, or 64 with at least 6 key tiles, where the
   //   pipelined loop's steady state counts: 8 waves x 32 queries per workgroup
   //   (240 items x 1077 tokens of head_dim 64: 27.5 against 39.1 for the
   //   four-wave kernel; 144 items x 1500 of 128: 53 against 112; 160 x 400 of 72:
   //   15.4 against 20.4; 96 x 333 of 72: 13.1 against 13.0; 128 x 256: 12.3
-  //   against 11.3);
+  //   against 11.3; at the line, head_dim 128: 64 items x 390 19.7 against 20.6,
+  //   64 x 512 21.3 against 20.5, 96 x 640 23.8 against 24.5, 128 x 390 20.7
+  //   against 24.6);
   // - else 4 waves x 32 queries, which spreads short sequences over twice as
   //   many workgroups.
   const long items = (long)((a.Tj + 255) / 256) * a.H * a.B;

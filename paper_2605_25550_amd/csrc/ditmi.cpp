@@ -276,8 +276,8 @@ static double tail_rounds(long t0, int S) { return (double)(t0 / 256) + 1.0 / S 
 // measured (K 384..4608, 64..512 rows): 4.2 us + 11.5 us per MB of operand rows
 // a workgroup reads, (BM + BN) K / S 2 bytes.  Among 64 x 32, 64 x 64, 64 x 96
 // (gemm_bf16_kg.hip) and 64 x 128 in S k-ranges, the least of that plus, with
-// S > 1, 3 us and the partial traffic at 5 TB/s for the reduction (which may
-// take the next LayerNorm along).  E.g. the output projection at 256 rows of
+// S > 1, 3 us and the partial traffic at 5 TB/s for the reduction (that it may
+// take the next LayerNorm along, a launch of 4 us, is not counted).  E.g. the output projection at 256 rows of
 // DiT-XL/2: 64 x 32 whole, 144 workgroups, 6.2 us against 6.4 + 3.6 for 64 x 128
 // in three ranges; fc2: 64 x 64 in three ranges 9.4 us, 64 x 128 in six 9.5.
 // 288 tiles, just over a round, are slower than 64 x 128 in every case (fc1 at

@@ -393,11 +393,15 @@ static hipError_t adaln_launch_t(AdaArgs& a, hipStream_t st) {
 }
 
 // Non-temporal weight loads (bf16) keep a matrix that is read once out of the
-// way of the block's other weights and activations: DiT-XL/2 block at 8
-// samples of 256 tokens 144.4 -> 138.9 us, joint block (226 MB of modulation
-// weights) 1282 -> 1264, steps unchanged.  Not where several passes over the samples read the
-// matrix again, nor for the small fused launches (one 16 MB matrix at one
-// sample: block 58.0 us with them, 56.9 without).
+// way of the block's other weights and activations, which then stay cached from
+// call to call: DiT-XL/2 block at 8 samples of 256 tokens 144.4 -> 138.9 us, joint
+// block (226 MB of modulation weights) 1282 -> 1264; steps of 12 blocks at hidden
+// 768 (85 MB) and 1 to 16 samples of 64 tokens 470-788 -> 429-715 (their adaLN
+// launch alone 20-25 -> 25-30); of 384 (21 MB, all cached) the same within 0.7%;
+// steps of 28 blocks unchanged.  Not where several passes over the samples read
+// the matrix again, nor for fused launches below 64 MB: whole blocks with and
+// without them at 16 MB 58.0 and 56.9 us, 28 MB 70.5 and 68.7, 57 MB 75.0 and
+// 72.5, but 100 MB 103 and 126, 113 MB 102 and 121.
 hipError_t launch_adaln(AdaArgs a, int dtype, bool fused, hipStream_t st) {
   if (dtype != 1) return adaln_launch_t<float, 1, true, false>(a, st);
   double bytes = 0;
@@ -592,8 +596,8 @@ hipError_t launch_cond_embed(int B, int D, const float* t, float t_val, const in
                        (const float*)table, h1, cond, st);
 }
 
-// Patch embedding x = z W^T + b (+ pos), fp32 accumulation in the order
-// b, p = 0 .. P-1, then pos.
+// Patch embedding x = z W^T + b (+ pos), fp32 accumulation from b on over the
+// channels (in order, but for the matrix cores' order within four), then pos.
 //
 // Up to 16 channels (patch_row_kernel): one workgroup per token row, the
 // patch vector in LDS, each lane a column.
